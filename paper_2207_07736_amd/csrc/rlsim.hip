@@ -39,6 +39,7 @@ struct rlsim {
     float* pad_s = nullptr;
     float* pad_a = nullptr;
     float* pad_b = nullptr;
+    uint32_t* stats_acc = nullptr;   // [blocks][8] shared block statistics of small policy calls, zero between calls
     std::string err;
 };
 
@@ -175,9 +176,11 @@ void free_state(rlsim* h)
     if (h->pad_s) (void)hipFree(h->pad_s);
     if (h->pad_a) (void)hipFree(h->pad_a);
     if (h->pad_b) (void)hipFree(h->pad_b);
+    if (h->stats_acc) (void)hipFree(h->stats_acc);
     h->cart = nullptr;
     h->ep = nullptr;
     h->pad_s = h->pad_a = h->pad_b = nullptr;
+    h->stats_acc = nullptr;
 }
 
 // Host-side layout conversion of the wide padding words, in 64 x 64 tiles:
@@ -297,10 +300,21 @@ hipError_t launch_chain_reset(const DevParams& p, uint32_t N, uint32_t n, float*
     return hipGetLastError();
 }
 
+// Which form of the policy kernel a batch runs (all give the same bits).  Small
+// batches leave SIMDs idle, and fewer environments per wave shorten the step;
+// large ones pay for the cart-pole steps that such waves repeat.  K = 32 with
+// learner outputs, us a launch with 16 / 32 / 64 environments per wave:
+//   bf16  4,096 envs 43 / 59 / 83; 49,152 86 / 91 / 87; 65,536 109 / 95 / 87
+//   fp32  4,096 envs 65 / 99 / 173; 49,152 130 / 148 / 177; 65,536 172 / 157 /
+//         178; 98,304 244 / 225 / 266; 131,072 318 / 298 / 283
+constexpr uint32_t kPolicyForm16Envs = 49152u;      // both weight types
+constexpr uint32_t kPolicyForm32EnvsF32 = 98304u;   // fp32 weights only
+
 template <class Mlp, bool REC, bool STATS>
 hipError_t launch_policy(const StepArgs& a, const PolicyArgs& w, hipStream_t s)
 {
-    const dim3 grid(grid_for(a.n)), block(kBlock);
+    constexpr uint32_t envs = Mlp::Form::kEnvs * (kBlock / 64);      // environments of a workgroup
+    const dim3 grid((a.n + envs - 1u) / envs), block(kBlock);
     if (w.p0 || w.logp || w.value) hipLaunchKernelGGL((k_policy_fused<Mlp, REC, STATS, true>), grid, block, 0, s, a, w);
     else hipLaunchKernelGGL((k_policy_fused<Mlp, REC, STATS, false>), grid, block, 0, s, a, w);
     return hipGetLastError();
@@ -313,6 +327,17 @@ hipError_t launch_policy_any(const StepArgs& a, const PolicyArgs& w, bool rec, b
     if (rec) return launch_policy<Mlp, true, false>(a, w, s);
     if (stats) return launch_policy<Mlp, false, true>(a, w, s);
     return launch_policy<Mlp, false, false>(a, w, s);
+}
+
+hipError_t launch_policy_form(const StepArgs& a, const PolicyArgs& w, bool bf16, bool rec, bool stats, hipStream_t s)
+{
+    if (bf16) {
+        if (a.n <= kPolicyForm16Envs) return launch_policy_any<MlpBf16<WaveForm16>>(a, w, rec, stats, s);
+        return launch_policy_any<MlpBf16<WaveForm64>>(a, w, rec, stats, s);
+    }
+    if (a.n <= kPolicyForm16Envs) return launch_policy_any<MlpF32<WaveForm16>>(a, w, rec, stats, s);
+    if (a.n <= kPolicyForm32EnvsF32) return launch_policy_any<MlpF32<WaveForm32>>(a, w, rec, stats, s);
+    return launch_policy_any<MlpF32<WaveForm64>>(a, w, rec, stats, s);
 }
 
 }  // namespace
@@ -396,6 +421,11 @@ int rlsim_create(uint32_t n_envs, uint32_t state_words, const rlsim_cfg* cfg, rl
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_s, pad_bytes);
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_a, pad_bytes);
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_b, pad_bytes);
+    if (!chain && D == 0u && n_envs <= std::max(kPolicyForm16Envs, kPolicyForm32EnvsF32)) {
+        const size_t acc_bytes = (size_t)grid_for(n_envs) * 8u * sizeof(uint32_t);
+        if (e == hipSuccess) e = hipMalloc(&h->stats_acc, acc_bytes);
+        if (e == hipSuccess) e = hipMemset(h->stats_acc, 0, acc_bytes);
+    }
     // the wide layout's row tails [D, Dp) stay zero for the handle's lifetime
     if (e == hipSuccess && h->wide) e = hipMemset(h->pad_s, 0, pad_bytes);
     if (e == hipSuccess && h->wide) e = hipMemset(h->pad_a, 0, pad_bytes);
@@ -524,9 +554,8 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
     a.stats = tr.block_stats;
     if (policy) {
         PolicyArgs w{policy->w1, policy->b1, policy->w2, policy->b2, policy->w3, policy->b3,
-                     policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value};
-        e = policy->dtype == RLSIM_BF16 ? launch_policy_any<MlpBf16>(a, w, rec, stats, h->stream)
-                                        : launch_policy_any<MlpF32>(a, w, rec, stats, h->stream);
+                     policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value, h->stats_acc};
+        e = launch_policy_form(a, w, policy->dtype == RLSIM_BF16, rec, stats, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "rlsim_step_fused: launch");
         h->t += K;
         return RLSIM_OK;
