@@ -236,10 +236,28 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const float* row, uin
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// A lane's W parameter pairs of one environment, drawn instead of loaded, with
+// the placement of replay_env (float4 i / 4 at word base + 64 i).  The row's tail
+// words past D keep the zero parameters they have in memory.
+template <int W>
+__device__ __forceinline__ void draw_lane_params(const StepArgs& a, uint32_t gid, uint32_t base, float (&pa)[W],
+                                                 float (&pb)[W])
+{
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const uint32_t j = base + (uint32_t)(i / 4) * 256u + (uint32_t)(i % 4);
+        draw_pad_params(a, gid, j, pa[i], pb[i]);
+        if (a.D % 4u != 0u && j >= a.D) {
+            pa[i] = 0.0f;
+            pb[i] = 0.0f;
+        }
+    }
+}
+
 // E environments replayed together (columns col0 .. col0 + E - 1 of block
 // blk): W words per lane per environment, loaded as float4 with the placement
 // of replay_env.
-template <int W, int E>
+template <int W, int E, bool DRAW>
 __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
                                              uint32_t steps, uint32_t blk, uint32_t col0)
 {
@@ -277,8 +295,8 @@ __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* 
                 u32x4 vs = {0u, 0u, 0u, 0u}, va = vs, vb = vs;
                 if (e < E) {
                     vs = __builtin_amdgcn_raw_buffer_load_b128(rs[e], jb, 0, 0);
-                    va = __builtin_amdgcn_raw_buffer_load_b128(ra[e], jb, 0, 0);
-                    vb = __builtin_amdgcn_raw_buffer_load_b128(rb[e], jb, 0, 0);
+                    if (!DRAW) va = __builtin_amdgcn_raw_buffer_load_b128(ra[e], jb, 0, 0);
+                    if (!DRAW) vb = __builtin_amdgcn_raw_buffer_load_b128(rb[e], jb, 0, 0);
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -287,6 +305,10 @@ __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* 
                     pb[e][i + q] = __uint_as_float(vb[q]);
                 }
             }
+        }
+        if (DRAW) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) draw_lane_params<W>(a, a.p.env0 + env[e], base, pa[e], pb[e]);
         }
         for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
             uint32_t ub[4], db[4];
@@ -318,7 +340,7 @@ __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* 
 // wave covers 1 KB contiguously), and the bits are wave-uniform, so each step
 // is a scalar branch and one FMA or multiply per word.  replay_env replays
 // column col of block blk.
-template <int W>
+template <int W, bool DRAW>
 __device__ __forceinline__ void replay_env(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
                                            uint32_t steps, uint32_t blk, uint32_t col)
 {
@@ -338,8 +360,9 @@ __device__ __forceinline__ void replay_env(const StepArgs& a, const uint32_t* ld
         for (int i = 0; i < W; i += 4) {
             const uint32_t jb = 4u * (base + (uint32_t)(i / 4) * 256u);
             const u32x4 vs = __builtin_amdgcn_raw_buffer_load_b128(rs, jb, 0, 0);
-            const u32x4 va = __builtin_amdgcn_raw_buffer_load_b128(ra, jb, 0, 0);
-            const u32x4 vb = __builtin_amdgcn_raw_buffer_load_b128(rb, jb, 0, 0);
+            u32x4 va = {0u, 0u, 0u, 0u}, vb = va;
+            if (!DRAW) va = __builtin_amdgcn_raw_buffer_load_b128(ra, jb, 0, 0);
+            if (!DRAW) vb = __builtin_amdgcn_raw_buffer_load_b128(rb, jb, 0, 0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 s[i + q] = __uint_as_float(vs[q]);
@@ -347,6 +370,7 @@ __device__ __forceinline__ void replay_env(const StepArgs& a, const uint32_t* ld
                 pb[i + q] = __uint_as_float(vb[q]);
             }
         }
+        if (DRAW) draw_lane_params<W>(a, a.p.env0 + env, base, pa, pb);
         for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
             const uint32_t ub = lds_u[w32 * kBlock + col];
             const uint32_t db = lds_d[w32 * kBlock + col];
@@ -488,6 +512,7 @@ __device__ __forceinline__ void replay_jt(float (&s)[8], const float (&pa)[8], c
 // Phase 2 of group g (columns 8 g .. 8 g + 7 of block blk): lane l holds word
 // l of each of the eight environments.  Row addresses are recomputed at the
 // store rather than held through the replay (fewer live registers).
+template <bool DRAW>
 __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t* lds_u, const uint8_t* lds_d,
                                                 uint32_t steps, uint32_t blk, uint32_t g)
 {
@@ -500,8 +525,16 @@ __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t
         const bool on = lane_on && env0 + (uint32_t)e < a.n;
         const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
         s[e] = on ? a.pad_s[row + lane] : 0.0f;
-        pa[e] = on ? a.pad_a[row + lane] : 0.0f;
-        pb[e] = on ? a.pad_b[row + lane] : 0.0f;
+        if (DRAW) {
+            draw_pad_params(a, a.p.env0 + env0 + (uint32_t)e, lane, pa[e], pb[e]);
+            if (lane >= a.D) {
+                pa[e] = 0.0f;
+                pb[e] = 0.0f;
+            }
+        } else {
+            pa[e] = on ? a.pad_a[row + lane] : 0.0f;
+            pb[e] = on ? a.pad_b[row + lane] : 0.0f;
+        }
     }
     for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
         const uint32_t* pu = reinterpret_cast<const uint32_t*>(lds_u + g * kChunk + w32 * 32u);
@@ -541,7 +574,7 @@ __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t
 // tests and branches, not its vector updates, set its pace, and more waves
 // hide more of them (D = 64 0.88-0.93 against 0.99-1.05 ms with one workgroup,
 // D = 512 2.00-2.04 against 2.17-2.29 ms).
-template <int W, int E, int NW, bool REC, bool STATS>
+template <int W, int E, int NW, bool DRAW, bool REC, bool STATS>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8)))
 void k_cartpole_wide(StepArgs a)
 {
@@ -582,10 +615,10 @@ void k_cartpole_wide(StepArgs a)
             g = __builtin_amdgcn_readfirstlane(g);
             if (g >= n_groups) break;
             if constexpr (W == 1)
-                replay_group_jt(a, reinterpret_cast<const uint8_t*>(lds_u[sl]),
+                replay_group_jt<DRAW>(a, reinterpret_cast<const uint8_t*>(lds_u[sl]),
                                 reinterpret_cast<const uint8_t*>(lds_d[sl]), steps, blk, g);
-            else if constexpr (E > 1) replay_group<W, E>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
-            else replay_env<W>(a, lds_u[sl], lds_d[sl], steps, blk, g);
+            else if constexpr (E > 1) replay_group<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
+            else replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g);
         }
     };
 

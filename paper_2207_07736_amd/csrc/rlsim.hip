@@ -225,6 +225,23 @@ constexpr uint32_t kSplitPadMinSteps = 64u;
 // (row offsets, chunk counts) far from overflow.
 constexpr uint32_t kMaxStateWords = (1u << 24) + 4u;
 
+// Most steps per call for which the wide kernel draws the padding parameters
+// again instead of loading them: short launches are bound by the bytes of the
+// state, long ones by the replay's updates, to which the draw adds (loaded /
+// drawn, us: D = 512, 262,144 envs, K = 1 413 / 215, 16 438 / 243, 64 521 / 387,
+// 128 655 / 600; D = 4,096, 73,242 envs, K = 1 1,160 / 702, 64 1,272 / 997,
+// 128 1,544 / 1,573).
+constexpr uint32_t kDrawMaxSteps = 96u;
+
+template <bool DRAW, bool REC, bool STATS>
+void launch_wide(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s)
+{
+    if (a.D <= 64u) hipLaunchKernelGGL((k_cartpole_wide<1, 8, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else if (a.D <= 256u) hipLaunchKernelGGL((k_cartpole_wide<4, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else if (a.D <= 512u) hipLaunchKernelGGL((k_cartpole_wide<8, 2, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_cartpole_wide<16, 1, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+}
+
 template <bool REC, bool STATS>
 hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s)
 {
@@ -253,10 +270,8 @@ hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s
         // Every shape fits the 64 VGPRs of eight waves per SIMD: two persistent
         // 16-wave workgroups per CU.
         const dim3 grid2(min(grid_for(a.n), 2u * cus)), block2(1024);
-        if (a.D <= 64u) hipLaunchKernelGGL((k_cartpole_wide<1, 8, 16, REC, STATS>), grid2, block2, 0, s, a);
-        else if (a.D <= 256u) hipLaunchKernelGGL((k_cartpole_wide<4, 4, 16, REC, STATS>), grid2, block2, 0, s, a);
-        else if (a.D <= 512u) hipLaunchKernelGGL((k_cartpole_wide<8, 2, 16, REC, STATS>), grid2, block2, 0, s, a);
-        else hipLaunchKernelGGL((k_cartpole_wide<16, 1, 16, REC, STATS>), grid2, block2, 0, s, a);
+        if (a.K <= kDrawMaxSteps) launch_wide<true, REC, STATS>(a, grid2, block2, s);
+        else launch_wide<false, REC, STATS>(a, grid2, block2, s);
     }
     return hipGetLastError();
 }
@@ -547,6 +562,12 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
     a.pad_s = h->pad_s;
     a.pad_a = h->pad_a;
     a.pad_b = h->pad_b;
+    volatile float a_w = h->cfg.pad_a_high - h->cfg.pad_a_low;
+    volatile float b_w = h->cfg.pad_b_high - h->cfg.pad_b_low;
+    a.pad_a_lo = h->cfg.pad_a_low;
+    a.pad_a_width = a_w;
+    a.pad_b_lo = h->cfg.pad_b_low;
+    a.pad_b_width = b_w;
     a.obs = tr.obs;
     a.action = tr.action;
     a.reward = tr.reward;
