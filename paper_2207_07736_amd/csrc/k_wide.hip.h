@@ -389,7 +389,8 @@ __device__ __forceinline__ void replay_env(const StepArgs& a, const uint32_t* ld
 }
 
 // ---------------------------------------------------------------------------
-// One padding word per lane (at most 64 words), eight environments per step.
+// One padding word per lane (at most 64 words), eight environments per step,
+// calls of more than 96 steps.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kJtGroup = 8;                     // environments per replay group
 
@@ -512,7 +513,6 @@ __device__ __forceinline__ void replay_jt(float (&s)[8], const float (&pa)[8], c
 // Phase 2 of group g (columns 8 g .. 8 g + 7 of block blk): lane l holds word
 // l of each of the eight environments.  Row addresses are recomputed at the
 // store rather than held through the replay (fewer live registers).
-template <bool DRAW>
 __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t* lds_u, const uint8_t* lds_d,
                                                 uint32_t steps, uint32_t blk, uint32_t g)
 {
@@ -525,16 +525,8 @@ __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t
         const bool on = lane_on && env0 + (uint32_t)e < a.n;
         const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
         s[e] = on ? a.pad_s[row + lane] : 0.0f;
-        if (DRAW) {
-            draw_pad_params(a, a.p.env0 + env0 + (uint32_t)e, lane, pa[e], pb[e]);
-            if (lane >= a.D) {
-                pa[e] = 0.0f;
-                pb[e] = 0.0f;
-            }
-        } else {
-            pa[e] = on ? a.pad_a[row + lane] : 0.0f;
-            pb[e] = on ? a.pad_b[row + lane] : 0.0f;
-        }
+        pa[e] = on ? a.pad_a[row + lane] : 0.0f;
+        pb[e] = on ? a.pad_b[row + lane] : 0.0f;
     }
     for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
         const uint32_t* pu = reinterpret_cast<const uint32_t*>(lds_u + g * kChunk + w32 * 32u);
@@ -551,6 +543,132 @@ __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t
     for (int e = 0; e < 8; ++e) {
         const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
         if (lane_on && env0 + (uint32_t)e < a.n) a.pad_s[row + lane] = s[e];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// One or two padding words per lane (at most 128 words): selection by masks.
+// ---------------------------------------------------------------------------
+// s <- fma(a, s, b) for action 1 and a s = fma(a, s, -0) for action 0: the
+// addend is taken from b or -0 by a wave-uniform mask, one v_bitop3_b32 (a
+// full-rate instruction; v_cndmask_b32 is half-rate), the mask one scalar bit
+// extract per environment.  No branch depends on an action.  Two vector
+// instructions per word instead of one: it pays up to two words per lane, where
+// the trees' and tables' jumps cost more (262,144 envs: D = 128 against four
+// words per lane, half of them empty, K = 500 1.17 -> 1.15 ms, K = 16 134 -> 87 us
+// with drawn parameters; D = 64 against the jump table, drawn parameters in both,
+// K = 1 38 -> 34 us, K = 16 63 -> 59, but K = 64 135 -> 142 and K = 500, loaded,
+// 840 -> 911: the table keeps the long calls).
+__device__ __forceinline__ float masked_update(float a, float s, float b, uint32_t mask)
+{
+    // (b & mask) | (-0 & ~mask)
+    const uint32_t add = __builtin_amdgcn_bitop3_b32(__float_as_uint(b), mask, 0x80000000u, 0xE2);
+    return __builtin_fmaf(a, s, __uint_as_float(add));
+}
+
+// One step of E environments, their bits in bit i of u and d (all uniform).
+template <int E, int W>
+__device__ __forceinline__ void masked_step(float (&s)[E][W], const float (&pa)[E][W], const float (&pb)[E][W],
+                                            const uint32_t (&u)[E], const uint32_t (&d)[E], uint32_t dor, uint32_t i)
+{
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const uint32_t mask = (uint32_t)((int32_t)(u[e] << (31u - i)) >> 31);
+#pragma unroll
+        for (int w = 0; w < W; ++w) s[e][w] = masked_update(pa[e][w], s[e][w], pb[e][w], mask);
+    }
+    if ((dor >> i) & 1u) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const uint32_t keep = ((d[e] >> i) & 1u) - 1u;
+#pragma unroll
+            for (int w = 0; w < W; ++w) s[e][w] = __uint_as_float(__float_as_uint(s[e][w]) & keep);
+        }
+    }
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// Words j0 .. j0 + W - 1 of a row (0 past its end; rows are a multiple of four
+// words, so a pair is all in or all out).
+template <int W>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t row, uint32_t j0, float (&v)[W])
+{
+    if constexpr (W == 2) {
+        const u32x2 two = __builtin_amdgcn_raw_buffer_load_b64(row, 4u * j0, 0, 0);
+        v[0] = __uint_as_float(two[0]);
+        v[W - 1] = __uint_as_float(two[1]);
+    } else {
+        v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(row, 4u * j0, 0, 0));
+    }
+}
+
+// Phase 2 of columns col0 .. col0 + E - 1 of block blk: lane l holds words
+// W l .. W l + W - 1 of each environment.
+template <int W, int E, bool DRAW>
+__device__ __forceinline__ void replay_masked(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
+                                              uint32_t steps, uint32_t blk, uint32_t col0)
+{
+    static_assert(W == 1 || W == 2, "words per lane");
+    constexpr uint32_t kUnroll = 8;
+    const uint32_t lane = threadIdx.x % 64u, j0 = (uint32_t)W * lane;
+    const uint32_t env0 = blk * kBlock + col0;
+    float s[E][W], pa[E][W], pb[E][W];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
+        const uint32_t words = env0 + (uint32_t)e < a.n ? a.Dp : 0u;
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, words), ra = row_rsrc(a.pad_a + row, words),
+                                     rb = row_rsrc(a.pad_b + row, words);
+        load_words<W>(rs, j0, s[e]);
+        if (DRAW) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                draw_pad_params(a, a.p.env0 + env0 + (uint32_t)e, j0 + (uint32_t)w, pa[e][w], pb[e][w]);
+                if (j0 + (uint32_t)w >= a.D) pa[e][w] = pb[e][w] = 0.0f;
+            }
+        } else {
+            load_words<W>(ra, j0, pa[e]);
+            load_words<W>(rb, j0, pb[e]);
+        }
+    }
+    for (uint32_t k = 0; k < steps; k += 32u) {
+        uint32_t u[E], d[E], dor = 0u;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            u[e] = __builtin_amdgcn_readfirstlane(lds_u[(k / 32u) * kBlock + col0 + (uint32_t)e]);
+            d[e] = __builtin_amdgcn_readfirstlane(lds_d[(k / 32u) * kBlock + col0 + (uint32_t)e]);
+            dor |= d[e];
+        }
+        uint32_t left = min(32u, steps - k);
+        for (; left >= kUnroll; left -= kUnroll) {
+#pragma unroll
+            for (uint32_t i = 0; i < kUnroll; ++i) masked_step<E, W>(s, pa, pb, u, d, dor, i);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                u[e] >>= kUnroll;
+                d[e] >>= kUnroll;
+            }
+            dor >>= kUnroll;
+        }
+        for (; left > 0u; --left) {
+            masked_step<E, W>(s, pa, pb, u, d, dor, 0u);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                u[e] >>= 1;
+                d[e] >>= 1;
+            }
+            dor >>= 1;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, env0 + (uint32_t)e < a.n ? a.Dp : 0u);
+        if constexpr (W == 2)
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(s[e][0]), __float_as_uint(s[e][W - 1])}, rs,
+                                                  4u * j0, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s[e][0]), rs, 4u * j0, 0, 0);
     }
 }
 
@@ -579,8 +697,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8)))
 void k_cartpole_wide(StepArgs a)
 {
     static_assert(NW >= 8 && NW <= 16, "the pipeline needs four stepping waves and at least four more");
-    static_assert(W == 1 || W == 4 || W == 8 || W == 16, "shapes that fit 64 VGPRs");
-    static_assert(W != 1 || E == (int)kJtGroup, "one word per lane takes the eight-environment jump table");
+    static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16, "shapes that fit 64 VGPRs");
+    // one word per lane: short calls (the ones that draw) replay by masks, long
+    // ones through the jump table
+    constexpr bool kTable = W == 1 && !DRAW;
+    static_assert(!kTable || E == (int)kJtGroup, "the jump table takes eight environments");
     __shared__ uint32_t lds_u[2][kChunkWords * kBlock];
     __shared__ uint32_t lds_d[2][kChunkWords * kBlock];
     __shared__ uint32_t next_group[2];
@@ -614,9 +735,10 @@ void k_cartpole_wide(StepArgs a)
             if (lane == 0u) g = atomicAdd(&next_group[sl], 1u);
             g = __builtin_amdgcn_readfirstlane(g);
             if (g >= n_groups) break;
-            if constexpr (W == 1)
-                replay_group_jt<DRAW>(a, reinterpret_cast<const uint8_t*>(lds_u[sl]),
+            if constexpr (kTable)
+                replay_group_jt(a, reinterpret_cast<const uint8_t*>(lds_u[sl]),
                                 reinterpret_cast<const uint8_t*>(lds_d[sl]), steps, blk, g);
+            else if constexpr (W <= 2) replay_masked<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
             else if constexpr (E > 1) replay_group<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
             else replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g);
         }
@@ -649,7 +771,7 @@ void k_cartpole_wide(StepArgs a)
                 uint32_t counts = 0u;
                 if (live) {
                     if (REC) core.set_rows(a, k0);
-                    if constexpr (W == 1) {
+                    if constexpr (kTable) {
                         ByteRecorder<STATS> rec{reinterpret_cast<uint8_t*>(lds_u[j & 1u]),
                                                 reinterpret_cast<uint8_t*>(lds_d[j & 1u]), lane, wave};
                         core.run(a.t0 + k0, steps, rec);

@@ -237,6 +237,7 @@ template <bool DRAW, bool REC, bool STATS>
 void launch_wide(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s)
 {
     if (a.D <= 64u) hipLaunchKernelGGL((k_cartpole_wide<1, 8, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else if (a.D <= 128u) hipLaunchKernelGGL((k_cartpole_wide<2, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
     else if (a.D <= 256u) hipLaunchKernelGGL((k_cartpole_wide<4, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
     else if (a.D <= 512u) hipLaunchKernelGGL((k_cartpole_wide<8, 2, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_cartpole_wide<16, 1, 16, DRAW, REC, STATS>), grid, block, 0, s, a);

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("D", [33, 64, 65, 254, 257, 511, 513, 1027, 2051])
+@pytest.mark.parametrize("D", [33, 64, 65, 126, 128, 129, 254, 257, 511, 513, 1027, 2051])
 def test_drawn_and_loaded_parameters(D):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
