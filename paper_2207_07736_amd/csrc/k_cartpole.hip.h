@@ -34,6 +34,8 @@ struct StepArgs {
     float* reward;       // [K][n]
     uint8_t* done;       // [K][n]
     uint32_t* stats;     // [ceil(n/256)][4]
+    uint32_t* stats_acc; // [ceil(n/256)][8] accumulators of workgroups that share a row of stats, zero between calls
+    uint32_t wide_log2;  // wide kernel: log2 of a block's environments, 3 .. 8
 };
 
 // The padding parameters a_j, b_j of word j of global environment gid, drawn
@@ -305,6 +307,29 @@ __device__ __forceinline__ void store_block_stats(uint32_t* stats, uint32_t blk,
     }
 }
 
+// Four lanes (q = 0 .. 3) of one wave add a block's sums to row `row` of the
+// block statistics, which `parts` blocks of fewer than 256 environments share:
+// through the handle's accumulators (zero between launches), written out and
+// zeroed again by the last of the parts to arrive.  All accesses are device-scope
+// atomic read-modify-writes, done where every XCD sees them; waiting for the
+// sums' old values orders them before the arrival.  A __threadfence() in its
+// place writes the XCD's L2 back once per workgroup (wide kernel, 65,536 envs,
+// D = 40, K = 1 in 512 blocks: 38 -> 11 us a launch).
+__device__ __forceinline__ void add_shared_stats(uint32_t* stats, uint32_t* acc, uint32_t row, uint32_t parts,
+                                                 uint32_t q, uint32_t sum)
+{
+    uint32_t* a = acc + (size_t)row * 8u;
+    const uint32_t old = atomicAdd(&a[q], sum);
+    uint32_t one = 1u;
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(one) : "v"(old) : "memory");
+    uint32_t arrived = 0u;
+    if (q == 0u) arrived = atomicAdd(&a[4], one);
+    if (__builtin_amdgcn_readfirstlane(arrived) == parts - 1u) {
+        stats[(size_t)row * 4u + q] = atomicExch(&a[q], 0u);
+        if (q == 0u) atomicExch(&a[4], 0u);
+    }
+}
+
 // One padding word, s <- a s + b u rounded once: fma(a, s, b) when u = 1 and
 // the product a s when u = 0.  fma(a, s, -0) equals the product bit for bit
 // (x + -0 = x for every x, including both zeros), so a per-lane action costs
@@ -515,9 +540,11 @@ void k_cartpole_split(StepArgs a)
 // Reset.
 // ---------------------------------------------------------------------------
 // Initial state of every environment (episode beginning at step 0).
-__global__ __launch_bounds__(kBlock) void k_reset_cart(DevParams p, uint32_t n, float* cart, uint32_t* ep)
+__global__ __launch_bounds__(kBlock) void k_reset_cart(DevParams p, uint32_t n, float* cart, uint32_t* ep,
+                                                       uint32_t* stats_acc)
 {
     const uint32_t env = blockIdx.x * kBlock + threadIdx.x;
+    if (stats_acc && threadIdx.x < 8u) stats_acc[(size_t)blockIdx.x * 8u + threadIdx.x] = 0u;
     if (env >= n) return;
     const uint4 w = philox(env + p.env0, 0u, STREAM_RESET, p.key0, p.key1);
     const size_t plane = n;

@@ -52,7 +52,6 @@ struct PolicyArgs {
     float* p0;          // [K][n] or null
     float* logp;        // [K][n] or null
     float* value;       // [K][n] or null
-    uint32_t* stats_acc;   // [ceil(n/256)][8] zeroed accumulators of the handle (WaveForm16)
 };
 
 // log pi(a) for two logits, from d = l1 - l0: with z = l_other - l_a,
@@ -614,9 +613,7 @@ struct PolicyRows {
 };
 
 // One row of the block statistics from the workgroups that share a
-// 256-environment block: each adds its sums to the handle's accumulators
-// (zero between launches), and the last to arrive writes the row and zeroes
-// them again.
+// 256-environment block.
 __device__ __forceinline__ void share_block_stats(uint32_t* stats, uint32_t* acc, uint32_t blk, uint32_t parts,
                                                   uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3)
 {
@@ -630,22 +627,11 @@ __device__ __forceinline__ void share_block_stats(uint32_t* stats, uint32_t* acc
         part[wave][3] = v3;
     }
     __syncthreads();
-    if (threadIdx.x == 0u) {
-        uint32_t* a = acc + (size_t)blk * 8u;
+    if (threadIdx.x < 4u) {
+        uint32_t sum = 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t sum = 0u;
-#pragma unroll
-            for (int w = 0; w < (int)(kBlock / 64); ++w) sum += part[w][q];
-            atomicAdd(&a[q], sum);
-        }
-        __threadfence();
-        if (atomicAdd(&a[4], 1u) == parts - 1u) {
-            __threadfence();
-#pragma unroll
-            for (int q = 0; q < 4; ++q) stats[(size_t)blk * 4u + q] = atomicExch(&a[q], 0u);
-            atomicExch(&a[4], 0u);
-        }
+        for (int w = 0; w < (int)(kBlock / 64); ++w) sum += part[w][threadIdx.x];
+        add_shared_stats(stats, acc, blk, parts, threadIdx.x, sum);
     }
 }
 
@@ -712,7 +698,7 @@ void k_policy_fused(StepArgs a, PolicyArgs w)
             constexpr uint32_t kShare = (uint32_t)kBlock / (F::kEnvs * (kBlock / 64));     // workgroups per block
             const uint32_t groups = (a.n + kBlock / kShare - 1u) / (kBlock / kShare);
             const uint32_t b256 = blk / kShare;
-            share_block_stats(a.stats, w.stats_acc, b256, min(kShare, groups - b256 * kShare), c0, c1, c2, c3);
+            share_block_stats(a.stats, a.stats_acc, b256, min(kShare, groups - b256 * kShare), c0, c1, c2, c3);
         }
     }
 }

@@ -270,7 +270,7 @@ __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* 
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         col[e] = col0 + (uint32_t)(e < E ? e : 0);
-        env[e] = blk * kBlock + col[e];
+        env[e] = (blk << a.wide_log2) + col[e];
         live[e] = e < E && env[e] < a.n;
     }
     // wave-uniform buffer resources over the E rows (scalar registers): each
@@ -339,58 +339,55 @@ __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* 
 // 4 l + 256 q .. +3 of a 64 W-word chunk, so each float4 load and store of the
 // wave covers 1 KB contiguously), and the bits are wave-uniform, so each step
 // is a scalar branch and one FMA or multiply per word.  replay_env replays
-// column col of block blk.
+// chunk c of column col of block blk.
 template <int W, bool DRAW>
 __device__ __forceinline__ void replay_env(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
-                                           uint32_t steps, uint32_t blk, uint32_t col)
+                                           uint32_t steps, uint32_t blk, uint32_t col, uint32_t c)
 {
     static_assert(W % 4 == 0, "bad wide-padding shape");
     const uint32_t lane = threadIdx.x % 64u;
     const uint32_t chunk_words = 64u * W;
-    const uint32_t n_chunks = (a.Dp + chunk_words - 1u) / chunk_words;
-    const uint32_t env = blk * kBlock + col;
+    const uint32_t env = (blk << a.wide_log2) + col;
     const size_t row = (size_t)env * a.Dp;
     const uint32_t words = env < a.n ? a.Dp : 0u;
     const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, words), ra = row_rsrc(a.pad_a + row, words),
                                  rb = row_rsrc(a.pad_b + row, words);
-    for (uint32_t c = 0; c < n_chunks; ++c) {
-        const uint32_t base = c * chunk_words + 4u * lane;
-        float s[W], pa[W], pb[W];
+    const uint32_t base = c * chunk_words + 4u * lane;
+    float s[W], pa[W], pb[W];
 #pragma unroll
-        for (int i = 0; i < W; i += 4) {
-            const uint32_t jb = 4u * (base + (uint32_t)(i / 4) * 256u);
-            const u32x4 vs = __builtin_amdgcn_raw_buffer_load_b128(rs, jb, 0, 0);
-            u32x4 va = {0u, 0u, 0u, 0u}, vb = va;
-            if (!DRAW) va = __builtin_amdgcn_raw_buffer_load_b128(ra, jb, 0, 0);
-            if (!DRAW) vb = __builtin_amdgcn_raw_buffer_load_b128(rb, jb, 0, 0);
+    for (int i = 0; i < W; i += 4) {
+        const uint32_t jb = 4u * (base + (uint32_t)(i / 4) * 256u);
+        const u32x4 vs = __builtin_amdgcn_raw_buffer_load_b128(rs, jb, 0, 0);
+        u32x4 va = {0u, 0u, 0u, 0u}, vb = va;
+        if (!DRAW) va = __builtin_amdgcn_raw_buffer_load_b128(ra, jb, 0, 0);
+        if (!DRAW) vb = __builtin_amdgcn_raw_buffer_load_b128(rb, jb, 0, 0);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                s[i + q] = __uint_as_float(vs[q]);
-                pa[i + q] = __uint_as_float(va[q]);
-                pb[i + q] = __uint_as_float(vb[q]);
-            }
+        for (int q = 0; q < 4; ++q) {
+            s[i + q] = __uint_as_float(vs[q]);
+            pa[i + q] = __uint_as_float(va[q]);
+            pb[i + q] = __uint_as_float(vb[q]);
         }
-        if (DRAW) draw_lane_params<W>(a, a.p.env0 + env, base, pa, pb);
-        for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
-            const uint32_t ub = lds_u[w32 * kBlock + col];
-            const uint32_t db = lds_d[w32 * kBlock + col];
-            const uint32_t m = min(32u, steps - w32 * 32u);
-            replay_uniform<W>(s, pa, pb, __builtin_amdgcn_readfirstlane(ub), __builtin_amdgcn_readfirstlane(db),
-                              __builtin_amdgcn_readfirstlane(m));
-        }
+    }
+    if (DRAW) draw_lane_params<W>(a, a.p.env0 + env, base, pa, pb);
+    for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
+        const uint32_t ub = lds_u[w32 * kBlock + col];
+        const uint32_t db = lds_d[w32 * kBlock + col];
+        const uint32_t m = min(32u, steps - w32 * 32u);
+        replay_uniform<W>(s, pa, pb, __builtin_amdgcn_readfirstlane(ub), __builtin_amdgcn_readfirstlane(db),
+                          __builtin_amdgcn_readfirstlane(m));
+    }
 #pragma unroll
-        for (int i = 0; i < W; i += 4) {
-            const uint32_t jb = 4u * (base + (uint32_t)(i / 4) * 256u);
-            const u32x4 v = {__float_as_uint(s[i]), __float_as_uint(s[i + 1]), __float_as_uint(s[i + 2]),
-                             __float_as_uint(s[i + 3])};
-            __builtin_amdgcn_raw_buffer_store_b128(v, rs, jb, 0, 0);
-        }
+    for (int i = 0; i < W; i += 4) {
+        const uint32_t jb = 4u * (base + (uint32_t)(i / 4) * 256u);
+        const u32x4 v = {__float_as_uint(s[i]), __float_as_uint(s[i + 1]), __float_as_uint(s[i + 2]),
+                         __float_as_uint(s[i + 3])};
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, jb, 0, 0);
     }
 }
 
 // ---------------------------------------------------------------------------
 // One padding word per lane (at most 64 words), eight environments per step,
-// calls of more than 96 steps.
+// calls that load the parameters.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kJtGroup = 8;                     // environments per replay group
 
@@ -517,7 +514,7 @@ __device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t
                                                 uint32_t steps, uint32_t blk, uint32_t g)
 {
     const uint32_t lane = threadIdx.x % 64u;
-    const uint32_t env0 = blk * kBlock + g * kJtGroup;
+    const uint32_t env0 = (blk << a.wide_log2) + g * kJtGroup;
     const bool lane_on = lane < a.Dp;
     float s[8], pa[8], pb[8];
 #pragma unroll
@@ -612,7 +609,7 @@ __device__ __forceinline__ void replay_masked(const StepArgs& a, const uint32_t*
     static_assert(W == 1 || W == 2, "words per lane");
     constexpr uint32_t kUnroll = 8;
     const uint32_t lane = threadIdx.x % 64u, j0 = (uint32_t)W * lane;
-    const uint32_t env0 = blk * kBlock + col0;
+    const uint32_t env0 = (blk << a.wide_log2) + col0;
     float s[E][W], pa[E][W], pb[E][W];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -674,7 +671,8 @@ __device__ __forceinline__ void replay_masked(const StepArgs& a, const uint32_t*
 
 // k_cartpole_wide<W, E, NW>: the two phases, overlapped across the blocks of a
 // persistent workgroup of NW waves (two workgroups per CU; workgroup g takes
-// the 256-env blocks g, g + G, ... of a grid of G).  A work item is one 512-step
+// the blocks g, g + G, ... of a grid of G; a block is 256 environments, or
+// fewer, 2^wide_log2, in batches that would not give every CU one of 256).  A work item is one 512-step
 // round of one block, and the workgroup's items are its blocks round by round.
 // In iteration j the first four waves run phase 1 of item j (the cart-pole loop
 // with its trajectory stores, the action and done bits into LDS slot j & 1);
@@ -698,8 +696,8 @@ void k_cartpole_wide(StepArgs a)
 {
     static_assert(NW >= 8 && NW <= 16, "the pipeline needs four stepping waves and at least four more");
     static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16, "shapes that fit 64 VGPRs");
-    // one word per lane: short calls (the ones that draw) replay by masks, long
-    // ones through the jump table
+    // one word per lane: calls that draw replay by masks, the others through
+    // the jump table
     constexpr bool kTable = W == 1 && !DRAW;
     static_assert(!kTable || E == (int)kJtGroup, "the jump table takes eight environments");
     __shared__ uint32_t lds_u[2][kChunkWords * kBlock];
@@ -707,7 +705,8 @@ void k_cartpole_wide(StepArgs a)
     __shared__ uint32_t next_group[2];
     __shared__ uint32_t blk_stats[2][4];
     const uint32_t G = gridDim.x, wg = blockIdx.x;
-    const uint32_t n_blocks = (a.n + kBlock - 1u) / kBlock;
+    const uint32_t n_blocks = ((a.n - 1u) >> a.wide_log2) + 1u;
+    const uint32_t width = 1u << a.wide_log2;       // environments of a block
     const uint32_t my_blocks = wg < n_blocks ? (n_blocks - wg + G - 1u) / G : 0u;
     const uint32_t rounds = (a.K + kChunk - 1u) / kChunk;
     const uint32_t n_items = my_blocks * rounds;
@@ -727,8 +726,10 @@ void k_cartpole_wide(StepArgs a)
         // which would make it, and every row address after it, per-lane
         const uint32_t blk = __builtin_amdgcn_readfirstlane(wg + m * G);
         const uint32_t k0 = r * kChunk, steps = min(kChunk, a.K - k0);
-        const uint32_t cols = min((uint32_t)kBlock, a.n - blk * kBlock);
-        const uint32_t n_groups = (cols + (uint32_t)E - 1u) / (uint32_t)E;
+        const uint32_t cols = min(width, a.n - (blk << a.wide_log2));
+        // one environment per wave (E = 1): a group is one 64 W-word chunk of it
+        const uint32_t n_chunks = (a.Dp + 64u * (uint32_t)W - 1u) / (64u * (uint32_t)W);
+        const uint32_t n_groups = E > 1 ? (cols + (uint32_t)E - 1u) / (uint32_t)E : cols * n_chunks;
         const uint32_t sl = i & 1u;
         for (;;) {
             uint32_t g = 0u;
@@ -740,7 +741,7 @@ void k_cartpole_wide(StepArgs a)
                                 reinterpret_cast<const uint8_t*>(lds_d[sl]), steps, blk, g);
             else if constexpr (W <= 2) replay_masked<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
             else if constexpr (E > 1) replay_group<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
-            else replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g);
+            else replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g / n_chunks, g % n_chunks);
         }
     };
 
@@ -751,8 +752,8 @@ void k_cartpole_wide(StepArgs a)
         uint32_t j = 0u;
         for (uint32_t m = 0; m < my_blocks; ++m) {
             const uint32_t blk = wg + m * G;
-            const uint32_t env = blk * kBlock + col;
-            const bool live = env < a.n;
+            const uint32_t env = (blk << a.wide_log2) + col;
+            const bool live = col < width && env < a.n;
             // the episode counts go through the recorder and LDS, not the core,
             // which keeps them out of the stepping loop's registers
             CartCore<REC, false> core(a.p, env);
@@ -811,8 +812,11 @@ void k_cartpole_wide(StepArgs a)
             if (STATS && j >= 1u && (j - 1u) % rounds == rounds - 1u && threadIdx.x < 4u * 64u + 4u &&
                 threadIdx.x >= 4u * 64u) {
                 const uint32_t m = (j - 1u) / rounds, q = threadIdx.x - 4u * 64u;
-                a.stats[(size_t)(wg + m * G) * 4u + q] = blk_stats[m & 1u][q];
+                const uint32_t blk = wg + m * G, share = 8u - a.wide_log2, row = blk >> share;
+                const uint32_t sum = blk_stats[m & 1u][q];
                 blk_stats[m & 1u][q] = 0u;
+                if (share == 0u) a.stats[(size_t)row * 4u + q] = sum;
+                else add_shared_stats(a.stats, a.stats_acc, row, min(1u << share, n_blocks - (row << share)), q, sum);
             }
             if (j >= 1u) replay_item(j - 1u);
             __syncthreads();

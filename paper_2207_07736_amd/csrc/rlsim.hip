@@ -39,7 +39,7 @@ struct rlsim {
     float* pad_s = nullptr;
     float* pad_a = nullptr;
     float* pad_b = nullptr;
-    uint32_t* stats_acc = nullptr;   // [blocks][8] shared block statistics of small policy calls, zero between calls
+    uint32_t* stats_acc = nullptr;   // [blocks][8] shared rows of block statistics, zeroed by a reset and by each call
     std::string err;
 };
 
@@ -225,13 +225,40 @@ constexpr uint32_t kSplitPadMinSteps = 64u;
 // (row offsets, chunk counts) far from overflow.
 constexpr uint32_t kMaxStateWords = (1u << 24) + 4u;
 
-// Most steps per call for which the wide kernel draws the padding parameters
-// again instead of loading them: short launches are bound by the bytes of the
-// state, long ones by the replay's updates, to which the draw adds (loaded /
-// drawn, us: D = 512, 262,144 envs, K = 1 413 / 215, 16 438 / 243, 64 521 / 387,
-// 128 655 / 600; D = 4,096, 73,242 envs, K = 1 1,160 / 702, 64 1,272 / 997,
-// 128 1,544 / 1,573).
-constexpr uint32_t kDrawMaxSteps = 96u;
+// Whether the wide kernel draws the padding parameters again instead of loading
+// them.  Short launches are bound by the bytes of the state, long ones by the
+// replay's updates, to which the draw adds; and a state that fits the 256 MB
+// last-level cache between calls loads faster than it draws.  Loaded / drawn, us
+// a launch, by the megabytes of the three arrays:
+//          D x envs                K = 1        K = 16       K = 64
+//   120    200 x  50,000         28 / 32       36 / 39       65 / 71
+//   126     40 x 262,144         34 / 37       56 / 60      138 / 143
+//   157    200 x  65,536         35 / 33       44 / 40       69 / 74
+//   201   4096 x   4,096         44 / 33       50 / 42       70 / 74
+//   240    400 x  50,000         56 / 50       65 / 60       88 / 101
+//   315    200 x 131,072         66 / 51       80 / 67      148 / 130
+//   600   1000 x  50,000        173 / 95      178 / 108     203 / 167
+// D = 512, 262,144 envs, K = 128: 655 / 600; D = 4,096, 73,242 envs: 1,544 / 1,573.
+bool draw_params(uint32_t n, uint32_t Dp, uint32_t K)
+{
+    const uint64_t bytes = 12ull * n * Dp;
+    return K <= (bytes < 150000000ull ? 0u : bytes < 300000000ull ? 32u : 96u);
+}
+
+// log2 of the environments in a block of the wide kernel: as few (down to the
+// jump table's eight) as still give every block a resident workgroup of its
+// own, 256 beyond that.  Blocks of 64 and more fill whole stepping waves and go
+// two to a CU; smaller ones leave lanes empty, and two per CU would step twice
+// the waves.  256 per block / this rule, us a launch: 1,024 envs D = 4,096
+// K = 1 161 / 13, K = 500 2,490 / 262, D = 40 K = 500 302 / 246; 20,011 envs
+// D = 400 K = 500 519 / 326; 65,536 envs D = 200 K = 500 412 / 387.  4,096 envs,
+// D = 200, 512 blocks of 8 / 256 of 16: K = 1 9.9 / 7.8, K = 500 263 / 225.
+uint32_t wide_log2(uint32_t n, uint32_t cus)
+{
+    uint32_t l = 3u;
+    while (l < 8u && ((n - 1u) >> l) + 1u > (l < 6u ? cus : 2u * cus)) ++l;
+    return l;
+}
 
 template <bool DRAW, bool REC, bool STATS>
 void launch_wide(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s)
@@ -270,9 +297,11 @@ hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s
         // last one, and 11.9-12.4 ms at D = 4,096 with 64 words at two waves).
         // Every shape fits the 64 VGPRs of eight waves per SIMD: two persistent
         // 16-wave workgroups per CU.
-        const dim3 grid2(min(grid_for(a.n), 2u * cus)), block2(1024);
-        if (a.K <= kDrawMaxSteps) launch_wide<true, REC, STATS>(a, grid2, block2, s);
-        else launch_wide<false, REC, STATS>(a, grid2, block2, s);
+        StepArgs b = a;
+        b.wide_log2 = wide_log2(a.n, cus);
+        const dim3 grid2(min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus)), block2(1024);
+        if (draw_params(a.n, a.Dp, a.K)) launch_wide<true, REC, STATS>(b, grid2, block2, s);
+        else launch_wide<false, REC, STATS>(b, grid2, block2, s);
     }
     return hipGetLastError();
 }
@@ -437,11 +466,10 @@ int rlsim_create(uint32_t n_envs, uint32_t state_words, const rlsim_cfg* cfg, rl
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_s, pad_bytes);
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_a, pad_bytes);
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_b, pad_bytes);
-    if (!chain && D == 0u && n_envs <= std::max(kPolicyForm16Envs, kPolicyForm32EnvsF32)) {
-        const size_t acc_bytes = (size_t)grid_for(n_envs) * 8u * sizeof(uint32_t);
-        if (e == hipSuccess) e = hipMalloc(&h->stats_acc, acc_bytes);
-        if (e == hipSuccess) e = hipMemset(h->stats_acc, 0, acc_bytes);
-    }
+    // the policy forms and wide blocks whose workgroups share a row of the block statistics
+    const bool shared = h->wide ? wide_log2(n_envs, h->cus) < 8u
+                                : !chain && D == 0u && n_envs <= std::max(kPolicyForm16Envs, kPolicyForm32EnvsF32);
+    if (e == hipSuccess && shared) e = hipMalloc(&h->stats_acc, (size_t)grid_for(n_envs) * 8u * sizeof(uint32_t));
     // the wide layout's row tails [D, Dp) stay zero for the handle's lifetime
     if (e == hipSuccess && h->wide) e = hipMemset(h->pad_s, 0, pad_bytes);
     if (e == hipSuccess && h->wide) e = hipMemset(h->pad_a, 0, pad_bytes);
@@ -470,7 +498,7 @@ int rlsim_reset(rlsim_t* h, uint64_t seed)
         e = launch_chain_reset(h->dp, h->links, h->n, h->cart, h->ep, h->stream);
     } else {
         hipLaunchKernelGGL(k_reset_cart, dim3(grid_for(h->n)), dim3(kBlock), 0, h->stream, h->dp, h->n, h->cart,
-                           h->ep);
+                           h->ep, h->stats_acc);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return hip_fail(h, e, "rlsim_reset: launch");
@@ -574,9 +602,10 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
     a.reward = tr.reward;
     a.done = tr.done;
     a.stats = tr.block_stats;
+    a.stats_acc = h->stats_acc;
     if (policy) {
         PolicyArgs w{policy->w1, policy->b1, policy->w2, policy->b2, policy->w3, policy->b3,
-                     policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value, h->stats_acc};
+                     policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value};
         e = launch_policy_form(a, w, policy->dtype == RLSIM_BF16, rec, stats, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "rlsim_step_fused: launch");
         h->t += K;
