@@ -275,6 +275,9 @@ hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s
 {
     const dim3 grid(grid_for(a.n)), block(kBlock);
     if (!wide) {
+        // register words in steps of four above 16: each unused one costs three
+        // instructions a step (D = 20 in 32 / in 20 words, 100,003 envs, K = 128: 86 / 73 us);
+        // 12 words in 12 were no faster than in 16 (76 / 68 us)
         if (a.D == 0u && REC && a.K >= kSplitMinSteps)
             hipLaunchKernelGGL((k_cartpole_split<0, STATS>), grid, dim3(2 * kBlock), 0, s, a);
         else if (a.D <= 4u && REC && a.K >= kSplitPadMinSteps)
@@ -283,6 +286,9 @@ hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s
         else if (a.D <= 4u) hipLaunchKernelGGL((k_cartpole_fused<4, REC, STATS>), grid, block, 0, s, a);
         else if (a.D <= 8u) hipLaunchKernelGGL((k_cartpole_fused<8, REC, STATS>), grid, block, 0, s, a);
         else if (a.D <= 16u) hipLaunchKernelGGL((k_cartpole_fused<16, REC, STATS>), grid, block, 0, s, a);
+        else if (a.D <= 20u) hipLaunchKernelGGL((k_cartpole_fused<20, REC, STATS>), grid, block, 0, s, a);
+        else if (a.D <= 24u) hipLaunchKernelGGL((k_cartpole_fused<24, REC, STATS>), grid, block, 0, s, a);
+        else if (a.D <= 28u) hipLaunchKernelGGL((k_cartpole_fused<28, REC, STATS>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((k_cartpole_fused<32, REC, STATS>), grid, block, 0, s, a);
     } else {
         // one environment per wave in the replay (wave-uniform bits), W words
