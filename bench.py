@@ -344,7 +344,9 @@ def fusion_sweeps(stream) -> dict:
         entry = {}
         for K in w["K"]:
             ms = _time_schedule(sim, traj, [K] * (T // K), stream, reps=2)
-            state_bytes = (40 + 16 * D) * n * (T // K)
+            # short calls on large states draw the parameters a and b instead of reading them
+            drawn = D > 32 and K <= 32 and 12 * D * n >= 150_000_000
+            state_bytes = (40 + (8 if drawn else 16) * D) * n * (T // K)
             entry[f"K{K}"] = {"ms": ms, "env_steps_per_s": n * T / (ms * 1e-3),
                               "algorithmic_GBs": (n * T * workloads.TRAJ_BYTES_PER_ENV_STEP + state_bytes) / (ms * 1e-3) / 1e9}
         ms_nt = _time_schedule(sim, None, [T], stream, reps=2)
