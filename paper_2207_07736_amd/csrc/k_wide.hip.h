@@ -1,7 +1,7 @@
 // k_wide.hip.h -- cart-pole with a wide padding state (D > 32 words per
 // environment, the state-size factor S of the paper's "Simulator Complexity"),
 // more than one thread's registers hold cheaply.  Each 512-step round of a block
-// of 256 environments runs the cart-pole loop one thread per environment and
+// of up to 256 environments runs the cart-pole loop one thread per environment and
 // records the action and done bits in LDS (phase 1); the padding recurrence is
 // then replayed from those bits with each environment's words spread over the
 // 64 lanes of a wave (phase 2), while the next round's phase 1 runs in other
@@ -672,8 +672,8 @@ __device__ __forceinline__ void replay_masked(const StepArgs& a, const uint32_t*
 // k_cartpole_wide<W, E, NW>: the two phases, overlapped across the blocks of a
 // persistent workgroup of NW waves (two workgroups per CU; workgroup g takes
 // the blocks g, g + G, ... of a grid of G; a block is 256 environments, or
-// fewer, 2^wide_log2, in batches that would not give every CU one of 256).  A work item is one 512-step
-// round of one block, and the workgroup's items are its blocks round by round.
+// fewer, 2^wide_log2, in batches that would not give every CU one of 256).  A
+// work item is one 512-step round of one block, and the workgroup's items are its blocks round by round.
 // In iteration j the first four waves run phase 1 of item j (the cart-pole loop
 // with its trajectory stores, the action and done bits into LDS slot j & 1);
 // the other waves replay item j - 1 from slot (j - 1) & 1, taking
