@@ -166,7 +166,12 @@ struct PolicyTables {
     bf16x8 vec[kVecs];
     alignas(16) float b1[64], b2[64];
     float w3[F32 ? 192 : 1];
-    uint32_t bad[kBlock / 64];      // fp32: waves that saw a non-finite W2
+    uint32_t bad[kBlock / 64];      // fp32: waves that saw a W2 past kSplitLimit
+    // Largest |W2| that the split hidden layer takes.  The activations are within
+    // [-1, 1], so below it 64 products sum to at most 2^126: no partial sum of any
+    // order can overflow, and no piece of a weight either (a finite weight above
+    // 3.3961e38 would round to an infinite first piece).
+    static constexpr float kSplitLimit = 0x1.0p120f;
 
     __device__ void fill(const PolicyArgs& w)
     {
@@ -177,7 +182,7 @@ struct PolicyTables {
             b2[tid] = w.b2 ? w.b2[tid] : 0.0f;
         }
         if constexpr (F32) {
-            bool finite = true;
+            bool fits = true;
 #pragma unroll
             for (uint32_t it = 0; it < 4u; ++it) {
                 const uint32_t q = tid + it * kBlock, r = q / 16u, c = 4u * (q % 16u);
@@ -188,7 +193,7 @@ struct PolicyTables {
                 for (int i = 0; i < 4; ++i) {
                     // w = p0 + p1 + p2 exactly, each rounded to nearest
                     const float v = run.v[i];
-                    finite = finite && __builtin_fabsf(v) <= 3.402823466e38f;
+                    fits = fits && __builtin_fabsf(v) <= kSplitLimit;      // NaN does not
                     const __bf16 p0 = to_bf16(v);
                     const float r1 = v - (float)p0;
                     const __bf16 p1 = to_bf16(r1);
@@ -201,7 +206,7 @@ struct PolicyTables {
                 for (uint32_t p = 0; p < 3u; ++p)
                     *reinterpret_cast<ushort4*>(t + p * kPieceVecs * 8u + slot) = piece[p];
             }
-            const bool wave_bad = __builtin_amdgcn_ballot_w64(!finite) != 0u;
+            const bool wave_bad = __builtin_amdgcn_ballot_w64(!fits) != 0u;
             if (tid % 64u == 0u) bad[tid / 64u] = wave_bad ? 1u : 0u;
             if (tid < 192u) {
                 const float* w3p = reinterpret_cast<const float*>(w.w3);
@@ -388,7 +393,7 @@ struct MlpF32 {
     float a1[F::kTiles][F::kTileRows / 16];
     float b3_0, b3_1, bv;
     const float* w2;        // for the plain layer 2
-    bool plain;             // some W2 is not finite: its pieces are not its sum
+    bool plain;             // some W2 is past the split's limit, or not a number
 
     __device__ void load(const PolicyArgs& w, uint32_t lane)
     {

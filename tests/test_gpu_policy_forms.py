@@ -94,8 +94,7 @@ def test_weights_at_any_element_address(dtype, shift):
 @pytest.mark.parametrize("n", [300, 50000, 98560])
 def test_fp32_hidden_weights_that_are_not_finite(n):
     """An infinite W2 entry saturates its unit to the sign of its input, a NaN one
-    makes every output NaN (action 1), as in plain fp32 arithmetic; the largest
-    finite weights stay finite.  The reference is 64-bit; fp32 sums of 64 terms
+    makes every output NaN (action 1), as in plain fp32 arithmetic.  The reference is 64-bit; fp32 sums of 64 terms
     below 1 in magnitude are within 64 * 2^-24 = 4e-6 of it."""
     w = policy_weights(9, 0.3)
     w["w2"] = w["w2"].copy()
@@ -114,3 +113,49 @@ def test_fp32_hidden_weights_that_are_not_finite(n):
     w["w2"][50, 50] = np.nan
     out, _ = _run(n, 1, 1, w, "f32", 2)
     assert np.all(np.isnan(out["policy_p0"])) and np.all(np.isnan(out["value"])) and np.all(out["action"] == 1)
+
+
+FLT_MAX = np.finfo(np.float32).max
+
+
+@pytest.mark.parametrize("n", [300, 50000, 98560])
+@pytest.mark.parametrize("entries", [
+    [(40, 2, -FLT_MAX)], [(11, 60, 3.397e38)],      # infinite when rounded to bfloat16
+    [(5, 33, 3.38e38), (5, 34, -1.0e37)]])          # finite in bfloat16 too
+def test_fp32_hidden_weights_that_are_very_large(n, entries):
+    """A very large finite W2 entry saturates its unit to the sign of its input
+    and every output stays finite, with no infinity among the weights."""
+    w = policy_weights(9, 0.3)
+    w["w2"] = w["w2"].copy()
+    for r, c, v in entries:
+        w["w2"][r, c] = v
+    _against_64_bits(n, w)
+
+
+@pytest.mark.parametrize("n", [300, 50000, 98560])
+def test_fp32_large_hidden_weights_that_cancel(n):
+    """Eight weights of 3e38 against eight of -3e38 on saturated units: added one
+    unit of each at a time they cancel, where the sum of either eight overflows."""
+    w = policy_weights(9, 0.3)
+    w["w1"], w["b1"], w["w2"], w["b2"] = (w[k].copy() for k in ("w1", "b1", "w2", "b2"))
+    w["w1"][:16], w["b1"][:16] = 0.0, 20.0              # h1 = 1 exactly
+    plus = [0, 1, 2, 3, 8, 9, 10, 11]
+    w["w2"][7], w["b2"][7] = 0.0, 0.0
+    w["w2"][7, :16] = -3.0e38
+    w["w2"][7, plus] = 3.0e38
+    _against_64_bits(n, w)
+
+
+def _against_64_bits(n, w):
+    """One step against the network in 64 bits.  fp32 sums of 64 terms below 1 in
+    magnitude are within 64 * 2^-24 = 4e-6 of it."""
+    out, _ = _run(n, 1, 1, w, "f32", 2)
+    obs = out["obs"][0].T.astype(np.float64)
+    f = {k: v.astype(np.float64) for k, v in w.items()}
+    h1 = np.tanh(obs @ f["w1"].T + f["b1"])
+    h2 = np.tanh(np.stack([(h1 * f["w2"][r]).sum(1) for r in range(64)], 1) + f["b2"])
+    logit = h2 @ f["w3"].T + f["b3"]
+    p0 = 1.0 / (1.0 + np.exp(logit[:, 1] - logit[:, 0]))
+    assert np.all(np.isfinite(p0))
+    assert np.max(np.abs(out["policy_p0"][0] - p0)) <= 4e-6
+    assert np.max(np.abs(out["value"][0] - (h2 @ f["wv"].T + f["bv"])[:, 0])) <= 3e-5
