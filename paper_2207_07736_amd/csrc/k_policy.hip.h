@@ -442,19 +442,26 @@ struct MlpF32 {
         for (int i = 0; i < 3; ++i) p[i] = __builtin_bit_cast(bf16x8, out[i]);
     }
 
-    // one K step of layer 2 in plain fp32: the group's eight units one after
-    // another, in the order (s, j, h) in both forms
-    __device__ void plain_step(int s, const float (&x)[8], uint32_t lane, typename F::Acc (&c2)[F::kTiles]) const
+    // one K step of layer 2 in plain fp32, eight units of every group in turn: the
+    // sum runs over (s 0..3, j, h) in every form.  A K step of WaveForm16 covers
+    // two s: the quarters of the wave that hold the other one supply zeros.
+    __device__ void plain_step(int step, const float (&x)[8], uint32_t lane, typename F::Acc (&c2)[F::kTiles]) const
     {
-        const uint32_t g = F::group(lane) + F::g_step(s);
+        const uint32_t g = F::group(lane) + F::g_step(step);
+        constexpr uint32_t kParts = F::kTileRows == 32 ? 1u : 2u;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t unit = 16u * (g / 2u) + 8u * ((uint32_t)j / 4u) + 4u * (g % 2u) + (uint32_t)j % 4u;
+        for (uint32_t part = 0; part < kParts; ++part) {
+            const bool on = kParts == 1u || lane / 32u == part;
 #pragma unroll
-            for (int M = 0; M < F::kTiles; ++M) {
-                const float a = w2[(F::a_row(lane) + F::a_step(M)) * 64u + unit];
-                if constexpr (F::kTileRows == 32) c2[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, x[j], c2[M], 0, 0, 0);
-                else c2[M] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, x[j], c2[M], 0, 0, 0);
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t unit = 16u * (g / 2u) + 8u * ((uint32_t)j / 4u) + 4u * (g % 2u) + (uint32_t)j % 4u;
+                const float b = on ? x[j] : 0.0f;
+#pragma unroll
+                for (int M = 0; M < F::kTiles; ++M) {
+                    const float w = w2[(F::a_row(lane) + F::a_step(M)) * 64u + unit], a = on ? w : 0.0f;
+                    if constexpr (F::kTileRows == 32) c2[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c2[M], 0, 0, 0);
+                    else c2[M] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c2[M], 0, 0, 0);
+                }
             }
         }
     }

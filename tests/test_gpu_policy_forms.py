@@ -94,8 +94,9 @@ def test_weights_at_any_element_address(dtype, shift):
 @pytest.mark.parametrize("n", [300, 50000, 98560])
 def test_fp32_hidden_weights_that_are_not_finite(n):
     """An infinite W2 entry saturates its unit to the sign of its input, a NaN one
-    makes every output NaN (action 1), as in plain fp32 arithmetic.  The reference is 64-bit; fp32 sums of 64 terms
-    below 1 in magnitude are within 64 * 2^-24 = 4e-6 of it."""
+    makes every output NaN (action 1), as in plain fp32 arithmetic.  The reference
+    is 64-bit; fp32 sums of 64 terms below 1 in magnitude are within
+    64 * 2^-24 = 4e-6 of it."""
     w = policy_weights(9, 0.3)
     w["w2"] = w["w2"].copy()
     w["w2"][3, 17], w["w2"][40, 2], w["w2"][11, 60] = np.inf, -np.inf, 3.0e38
@@ -116,6 +117,20 @@ def test_fp32_hidden_weights_that_are_not_finite(n):
 
 
 FLT_MAX = np.finfo(np.float32).max
+
+
+@pytest.mark.parametrize("large", [np.inf, FLT_MAX])
+def test_forms_agree_bit_for_bit_on_the_plain_layer(large):
+    """One W2 entry that the split layer does not take: its unit saturates, and
+    the finite units keep the same bits in every form."""
+    w, K, seed = policy_weights(21, 0.3), 9, 3
+    w["w2"] = w["w2"].copy()
+    w["w2"][3, 17] = large
+    whole, _ = _run(98560, K, 1, w, "f32", seed)            # 64 per wave
+    for env0, size in ((0, 49152), (98304, 67), (256, 49153), (0, 98304)):      # 16, 16, 32, 32
+        part, _ = _run(size, K, 1, w, "f32", seed, env0=env0)
+        for k in PLANES + ("state", "ep"):
+            assert _same(part[k], np.ascontiguousarray(whole[k][..., env0:env0 + size])), (k, env0, size)
 
 
 @pytest.mark.parametrize("n", [300, 50000, 98560])
