@@ -371,16 +371,23 @@ struct MlpBf16 {
 
 // ---------------------------------------------------------------------------
 // fp32 MLP.  What bounds it is the VALU (tanh) and the matrix pipe one after the
-// other: fp32 matrix instructions share the SIMD with fp32 vector ones.  Layer 1 runs on the fp32 matrix instructions and layer 3 on the
-// VALU; layer 2, nine tenths of the arithmetic, runs on the bf16 ones at 16
-// times the fp32 rate, with every operand split into three bfloat16 pieces
-// (8 + 8 + 8 bits, each rounded to nearest: the split is exact).  Six products
-// per pair are summed, in fp32; the three left out are below 2^-26 of the
-// product, an eighth of the rounding of an fp32 product.  1,048,576 environments,
-// K = 16, learner outputs: 1.50 -> 1.04 ms (102 -> 147 TFLOP/s of the network's
-// own arithmetic), error of the value head against 64 bits 3.3e-7 -> 2.6e-7.
+// other: fp32 matrix instructions share the SIMD with fp32 vector ones.  Layer 1
+// runs on the fp32 matrix instructions and layer 3 on the VALU; layer 2, nine
+// tenths of the arithmetic, runs on the bf16 ones at 16 times the fp32 rate, with
+// every operand split into three bfloat16 pieces (8 + 8 + 8 bits, each rounded to
+// nearest: the split is exact).  Of the nine products of the pieces the one left
+// out, of the two last pieces, is at most 2^-34 of the whole.  The seven small
+// ones are within 2^-7 of it and are summed on their own, so that only the eight
+// leading sums (one a group) and the last addition round at the result's scale,
+// where 64 fp32 products summed one by one round 64 times.  Error against 64 bits,
+// the value head of eight random networks, 98,560 environments: 6.9e-8 rms with
+// fp32 products, 6.4e-8 with these; one weight per row with a bias that cancels
+// it: within 2^-30 of the product.  1,048,576 environments, K = 16, learner
+// outputs: 1.49 ms with fp32 products, 1.18 ms with these (102 -> 129 TFLOP/s of
+// the network's own arithmetic); six products (the three largest left out reach
+// 2^-24 together) took 1.04 ms.
 // WaveForm64 takes its two column tiles one after the other: both at once need
-// 256 registers (1.18 ms), four waves per SIMD spill (1.17 ms).
+// 256 registers, and four waves per SIMD spill.
 // ---------------------------------------------------------------------------
 template <class F>
 struct MlpF32 {
@@ -507,9 +514,9 @@ struct MlpF32 {
                 }
             }
             Acc c2[F::kTiles];
-#pragma unroll
-            for (int M = 0; M < F::kTiles; ++M) c2[M] = tab.bias(offsetof(Tables, b2), M);
             if (__builtin_expect(plain, 0)) {
+#pragma unroll
+                for (int M = 0; M < F::kTiles; ++M) c2[M] = tab.bias(offsetof(Tables, b2), M);
                 uint32_t at_lane = lane;
                 asm volatile("" : "+v"(at_lane));       // no address of this path outside it
 #pragma unroll
@@ -520,8 +527,13 @@ struct MlpF32 {
                     plain_step(s, x, at_lane, c2);
                 }
             } else {
-                // four groups at a time, so that every form adds them in one order
+                // the small products, smallest first within four groups; the row
+                // tiles' chains alternate
                 constexpr int kHalf = F::kSteps / 2;
+                constexpr int kW[7] = {2, 1, 2, 0, 1, 1, 0}, kX[7] = {1, 2, 0, 2, 1, 0, 1};
+                bf16x8 lead[F::kSteps];
+#pragma unroll
+                for (int M = 0; M < F::kTiles; ++M) c2[M] = Acc{};
 #pragma unroll
                 for (int s0 = 0; s0 < F::kSteps; s0 += kHalf) {
                     bf16x8 p[kHalf][3];
@@ -532,16 +544,25 @@ struct MlpF32 {
                         for (int j = 0; j < 8; ++j)
                             x[j] = tanh_fast(c1[F::tile_of(s0 + i, j)][F::reg_of(s0 + i, j)]);
                         split(x, p[i]);
+                        lead[s0 + i] = p[i][0];
                     }
-                    // smallest products first; the row tiles' chains alternate
-                    constexpr int kW[6] = {2, 0, 1, 1, 0, 0}, kX[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-                    for (int pr = 0; pr < 6; ++pr)
+                    for (int pr = 0; pr < 7; ++pr)
 #pragma unroll
                         for (int i = 0; i < kHalf; ++i)
 #pragma unroll
                             for (int M = 0; M < F::kTiles; ++M)
                                 c2[M] = F::mfma(tab.hidden(kW[pr], s0 + i, M), p[i][kX[pr]], c2[M]);
+                }
+                // 52 bytes of scratch in the two-tile form without it
+                if constexpr (F::kCols == 2) __builtin_amdgcn_sched_barrier(0);
+                // the leading products on the bias, and the small ones' sum
+#pragma unroll
+                for (int M = 0; M < F::kTiles; ++M) {
+                    Acc c = tab.bias(offsetof(Tables, b2), M);
+#pragma unroll
+                    for (int s = 0; s < F::kSteps; ++s) c = F::mfma(tab.hidden(0, s, M), lead[s], c);
+                    c2[M] += c;
                 }
             }
             // layer 3 on the VALU: each group's units in order, then the groups

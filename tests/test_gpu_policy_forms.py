@@ -174,3 +174,43 @@ def _against_64_bits(n, w):
     assert np.all(np.isfinite(p0))
     assert np.max(np.abs(out["policy_p0"][0] - p0)) <= 4e-6
     assert np.max(np.abs(out["value"][0] - (h2 @ f["wv"].T + f["bv"])[:, 0])) <= 3e-5
+
+
+@pytest.mark.parametrize("n", [256, 50176, 98560])
+def test_fp32_hidden_products_are_whole(n):
+    """One hidden weight per row and a bias that cancels most of the product:
+    the fp32 layer keeps every bit of both factors.  What is left out of a product
+    is below 2^-34 of it, and its small parts (within 2^-7 of it) are summed in
+    eight fp32 additions: 8 * 2^-24 * 2^-7 = 2^-28 together.  The sum of its
+    leading part and the bias is exact where they cancel.  S = 2^12 shows 2^-28 of
+    a product as 1.5e-5 to 3e-5 of the unit's input, against 1.3e-6 that its tanh
+    (2.5e-7, through a slope of 0.19 or more) hides.  Three of the nine products of
+    the bfloat16 pieces left out, or all summed on the bias, show as 2^-24 and more."""
+    S = 4096.0
+    rng = np.random.default_rng(0)
+    for unit in range(0, 64, 7):
+        c = np.float32(np.arctanh(rng.uniform(0.55, 0.95)))
+        centre = np.tanh(np.float64(c))
+        # the unit's exact h1, read through a weight that is a power of two
+        b = np.float64(np.float32(S * centre))
+        z = _one_unit(n, unit, c, S, b)
+        x = np.rint((z + b) * 4096.0) / 4096.0 / S      # h1 >= 0.5 is a multiple of 2^-24
+        for w in (1.0038986, 1.0 + 2.0 ** -8 - 2.0 ** -17, rng.uniform(1.0, 2.0)):
+            w = np.float64(np.float32(S * w))
+            b = np.float64(np.float32(w * centre))
+            got = _one_unit(n, unit, c, w, b)
+            use = (np.abs(z) < 1.4) & (np.abs(got) < 1.4)
+            assert use.sum() > n // 4
+            err = np.abs(got - (w * x - b))[use]
+            assert np.all(err <= 2.0 ** -28 * w * x[use] + 2.0e-6), (unit, w, err.max())
+
+
+def _one_unit(n, unit, c, weight, minus_bias):
+    """Layer-2 input of hidden unit `unit` for n environments whose h1 there is
+    tanh(c + 0.002 x) and its only weight `weight`."""
+    zero = dict(w1=(64, 4), b1=64, w2=(64, 64), b2=64, w3=(2, 64), b3=2, wv=(1, 64), bv=1)
+    w = {k: np.zeros(v, dtype=np.float32) for k, v in zero.items()}
+    w["w1"][unit, 0], w["b1"][unit] = 0.002, c
+    w["w2"][unit, unit], w["b2"][unit], w["wv"][0, unit] = weight, -minus_bias, 1.0
+    out, _ = _run(n, 1, 1, w, "f32", 3)
+    return np.arctanh(np.clip(out["value"][0].astype(np.float64), -1.0 + 1e-9, 1.0 - 1e-9))
