@@ -299,13 +299,29 @@ struct MlpBf16 {
     using Tables = PolicyTables<false>;
     using Lane = LaneTables<F, Tables>;
     static constexpr int kWaves = 2;     // waves per SIMD its registers are sized for
-    float b3_0, b3_1, bv;
+    // Held across the steps: the output layer's start value (left to itself the
+    // compiler builds it again, eight 64-bit moves a step, for the second column
+    // tile) and, in WaveForm64, layer 1's weights.  With the core's own stores in
+    // WaveForm64, 262,144 environments, K = 128: 1,031 -> 1,010 us; 4,096
+    // environments, K = 64, learner outputs: 79 -> 76 us.
+    static constexpr bool kHoldFirst = F::kEnvs == 64;
+    typename F::Acc out0;
+    bf16x8 a1[kHoldFirst ? F::kTiles : 1];
 
     __device__ void load(const PolicyArgs& w, uint32_t)
     {
-        b3_0 = w.b3 ? w.b3[0] : 0.0f;
-        b3_1 = w.b3 ? w.b3[1] : 0.0f;
-        bv = w.bv ? w.bv[0] : 0.0f;
+        out0 = typename F::Acc{};
+        out0[0] = w.b3 ? w.b3[0] : 0.0f;
+        out0[1] = w.b3 ? w.b3[1] : 0.0f;
+        out0[2] = w.bv ? w.bv[0] : 0.0f;
+        asm volatile("" : "+v"(out0));
+    }
+    __device__ void after_fill(const Tables&, const Lane& lane_tab)
+    {
+        if constexpr (kHoldFirst) {
+#pragma unroll
+            for (int M = 0; M < F::kTiles; ++M) a1[M] = lane_tab.first(M);
+        }
     }
 
     // Logit difference d = l1 - l0 and value v of this lane's environment; obs
@@ -332,7 +348,7 @@ struct MlpBf16 {
             Acc c1[F::kTiles];
 #pragma unroll
             for (int M = 0; M < F::kTiles; ++M)
-                c1[M] = F::mfma(tab.first(M), bin, tab.bias(offsetof(Tables, b1), M));
+                c1[M] = F::mfma(kHoldFirst ? a1[M] : tab.first(M), bin, tab.bias(offsetof(Tables, b1), M));
             // layer 2
             Acc c2[F::kTiles];
 #pragma unroll
@@ -347,10 +363,7 @@ struct MlpBf16 {
                     c2[M] = F::mfma(tab.hidden(0, s, M), b, c2[M]);
             }
             // layer 3: registers 0-2 of every lane are its column's outputs
-            Acc c3 = {};
-            c3[0] = b3_0;
-            c3[1] = b3_1;
-            c3[2] = bv;
+            Acc c3 = out0;
 #pragma unroll
             for (int s = 0; s < F::kSteps; ++s) {
                 bf16x8 b;
@@ -414,7 +427,7 @@ struct MlpF32 {
         bv = w.bv ? w.bv[0] : 0.0f;
         w2 = reinterpret_cast<const float*>(w.w2);
     }
-    __device__ void after_fill(const Tables& tab)
+    __device__ void after_fill(const Tables& tab, const Lane&)
     {
         uint32_t any = 0u;
 #pragma unroll
@@ -687,7 +700,10 @@ void k_policy_fused(StepArgs a, PolicyArgs w)
     const uint32_t env = (blk * (kBlock / 64u) + threadIdx.x / 64u) * (uint32_t)F::kEnvs + lane % (uint32_t)F::kEnvs;
     const bool live = env < a.n;
     const DevParams& p = a.p;
-    CartCore<false, STATS> core(p, env);
+    // WaveForm64: every lane owns its environment, and the core stores the rows
+    // itself (262,144 environments, K = 64: 519 -> 515 us against PolicyRows there)
+    constexpr bool kWhole = F::kEnvs == 64;
+    CartCore<REC && kWhole, STATS> core(p, env);
     if (live) {
         core.load(a);
     } else {
@@ -696,10 +712,12 @@ void k_policy_fused(StepArgs a, PolicyArgs w)
         core.ep_start = 0u;
     }
     const bool own = live && lane < (uint32_t)F::kEnvs;
-    PolicyRows<REC> rows{own, env * 4u, env, a.n, a.obs, a.action, a.reward, a.done};
+    if (REC && kWhole) core.set_rows(a, 0);
+    NoPad nopad;
+    PolicyRows<REC && !kWhole> rows{own, env * 4u, env, a.n, a.obs, a.action, a.reward, a.done};
     __syncthreads();
-    if constexpr (Mlp::Tables::kPieces == 3u) mlp.after_fill(tab);
     typename Mlp::Lane lane_tab(tab, lane);
+    mlp.after_fill(tab, lane_tab);
 
     size_t out_row = 0u;        // wave-uniform, as the row pointers
     uint4 pw = make_uint4(0u, 0u, 0u, 0u);
@@ -717,9 +735,14 @@ void k_policy_fused(StepArgs a, PolicyArgs w)
             if (w.logp) *at(w.logp + out_row, env * 4u) = log_pi(d, act);
             if (w.value) *at(w.value + out_row, env * 4u) = v;
         }
-        core.step_with(act, rows);
+        if constexpr (kWhole) {
+            if (live) core.step_with(act, nopad);
+            if (REC) core.advance_rows();
+        } else {
+            core.step_with(act, rows);
+            if (REC) rows.advance();
+        }
         if (OUT) out_row += a.n;
-        if (REC) rows.advance();
     }
     if (own) core.store(a);
     if (STATS) {
