@@ -2,8 +2,8 @@
  * rlsim_probe.h -- C ABI of the measurement aids beside librlsim.so
  * (librlsim_probe.so): the store-only probe of the trajectory layout, a
  * read/write stream probe, the error probe of the policy kernel's
- * elementwise functions, an instruction-rate probe and a fill probe of store
- * kernel shapes.
+ * elementwise functions, an instruction-rate probe, a fill probe of store
+ * kernel shapes and a report of the kernel forms that the library chooses.
  *
  * The fused simulator kernel's unavoidable work is writing the trajectory
  * (section "Simulator Kernel Fusion": fusion removes the state round trips,
@@ -131,6 +131,18 @@ int rlsim_probe_wall_clock_khz(uint32_t* khz);
  * Errors: -1 if n4 == 0, per_thread == 0 or > 2^20, the grid would reach 2^31
  * workgroups, or dst is NULL or not 16-byte aligned; -3 if the launch fails. */
 int rlsim_probe_fill(uint64_t n4, uint32_t per_thread, float* dst, void* stream);
+
+/* Which kernel form rlsim_step_fused runs for n cart-pole environments with D
+ * padding words, K steps and a trajectory or none (0 / 1), on a device with
+ * `cus` compute units (the library's own rules; every form gives the same
+ * results). */
+typedef struct {
+    uint32_t register_words;   /* D <= 32: padding words a thread holds (0: none) */
+} rlsim_dispatch;
+
+/* Fill *out (HOST memory); runs nothing on a device.  Errors: -1 if n == 0,
+ * K == 0, cus == 0 or out is NULL. */
+int rlsim_probe_dispatch(uint32_t n, uint32_t D, uint32_t K, uint32_t trajectory, uint32_t cus, rlsim_dispatch* out);
 
 #ifdef __cplusplus
 }

@@ -12,6 +12,7 @@
 #include <string>
 #include <vector>
 
+#include "dispatch.h"
 #include "k_chain.hip.h"
 #include "k_policy.hip.h"
 #include "k_wide.hip.h"
@@ -205,13 +206,6 @@ bool aligned4(const void* ptr) { return ((uintptr_t)ptr & 3u) == 0u; }
 
 unsigned grid_for(uint32_t n) { return (n + kBlock - 1u) / kBlock; }
 
-// Largest padding count of the register-resident (one thread per env) kernel;
-// above it the two-phase wide kernel holds the words.  (262,144 envs x 500
-// steps: D = 32 0.82-0.87 ms in registers; the wide kernel's eight-environment
-// jump table, one word per lane, costs the same at every D up to 64, 0.88-0.94 ms
-// at D = 48 and 64, where the register form, every thread updating all 64 words,
-// takes 1.07-1.13 ms.)
-constexpr uint32_t kMaxRegisterWords = 32u;
 // Fewest steps per call for which a trajectory-recording call runs the
 // warp-specialised kernel: without padding words, and with 1-4 padding words.
 // Below them the hand-over's pipeline fill and drain cost more than the faster
@@ -275,20 +269,18 @@ hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s
 {
     const dim3 grid(grid_for(a.n)), block(kBlock);
     if (!wide) {
-        // register words in steps of four above 16: each unused one costs three
-        // instructions a step (D = 20 in 32 / in 20 words, 100,003 envs, K = 128: 86 / 73 us);
-        // 12 words in 12 were no faster than in 16 (76 / 68 us)
+        const uint32_t words = register_words(a.D, a.n, a.K, REC, cus);
         if (a.D == 0u && REC && a.K >= kSplitMinSteps)
             hipLaunchKernelGGL((k_cartpole_split<0, STATS>), grid, dim3(2 * kBlock), 0, s, a);
         else if (a.D <= 4u && REC && a.K >= kSplitPadMinSteps)
             hipLaunchKernelGGL((k_cartpole_split<4, STATS>), grid, dim3(2 * kBlock), 0, s, a);
-        else if (a.D == 0u) hipLaunchKernelGGL((k_cartpole_fused<0, REC, STATS>), grid, block, 0, s, a);
-        else if (a.D <= 4u) hipLaunchKernelGGL((k_cartpole_fused<4, REC, STATS>), grid, block, 0, s, a);
-        else if (a.D <= 8u) hipLaunchKernelGGL((k_cartpole_fused<8, REC, STATS>), grid, block, 0, s, a);
-        else if (a.D <= 16u) hipLaunchKernelGGL((k_cartpole_fused<16, REC, STATS>), grid, block, 0, s, a);
-        else if (a.D <= 20u) hipLaunchKernelGGL((k_cartpole_fused<20, REC, STATS>), grid, block, 0, s, a);
-        else if (a.D <= 24u) hipLaunchKernelGGL((k_cartpole_fused<24, REC, STATS>), grid, block, 0, s, a);
-        else if (a.D <= 28u) hipLaunchKernelGGL((k_cartpole_fused<28, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 0u) hipLaunchKernelGGL((k_cartpole_fused<0, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 4u) hipLaunchKernelGGL((k_cartpole_fused<4, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 8u) hipLaunchKernelGGL((k_cartpole_fused<8, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 16u) hipLaunchKernelGGL((k_cartpole_fused<16, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 20u) hipLaunchKernelGGL((k_cartpole_fused<20, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 24u) hipLaunchKernelGGL((k_cartpole_fused<24, REC, STATS>), grid, block, 0, s, a);
+        else if (words == 28u) hipLaunchKernelGGL((k_cartpole_fused<28, REC, STATS>), grid, block, 0, s, a);
         else hipLaunchKernelGGL((k_cartpole_fused<32, REC, STATS>), grid, block, 0, s, a);
     } else {
         // one environment per wave in the replay (wave-uniform bits), W words

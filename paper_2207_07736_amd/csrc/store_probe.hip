@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include "rlsim_probe.h"
+#include "dispatch.h"
 #include "k_cartpole.hip.h"
 
 namespace rlsim_dev {
@@ -59,6 +60,16 @@ extern "C" int rlsim_probe_store(uint32_t n, uint32_t K, float* obs, uint8_t* ac
     const dim3 grid((n + rlsim_dev::kBlock - 1u) / rlsim_dev::kBlock), block(rlsim_dev::kBlock);
     hipLaunchKernelGGL(rlsim_dev::k_store_probe, grid, block, 0, (hipStream_t)stream, n, K, obs, action, reward, done);
     return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+extern "C" int rlsim_probe_dispatch(uint32_t n, uint32_t D, uint32_t K, uint32_t trajectory, uint32_t cus,
+                                    rlsim_dispatch* out)
+{
+    using namespace rlsim_dev;
+    if (n == 0u || K == 0u || cus == 0u || !out) return -1;
+    *out = rlsim_dispatch{};
+    if (D <= kMaxRegisterWords) out->register_words = register_words(D, n, K, trajectory != 0u, cus);
+    return 0;
 }
 
 #include "fill_probe.hip.h"

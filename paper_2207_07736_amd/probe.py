@@ -1,9 +1,8 @@
 """Thin ctypes binding of librlsim_probe.so (include/rlsim_probe.h): the
 store-only probe of the trajectory layout, a read/write stream probe, the
 error probe of the policy kernel's elementwise functions, the
-instruction-rate probe and the fill probe of store kernel shapes, measurement
-aids.  Argument
-marshalling only; fails loudly if the library has not been built."""
+instruction-rate probe, the fill probe of store kernel shapes and the report of
+the library's kernel forms, measurement aids.  Argument marshalling only; fails loudly if the library has not been built."""
 from __future__ import annotations
 
 import ctypes
@@ -12,8 +11,13 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 PROBE_LIB_PATH = os.path.join(_HERE, "librlsim_probe.so")
 PROBE_EXPORTS = ("rlsim_probe_store", "rlsim_probe_policy_math", "rlsim_probe_stream", "rlsim_probe_issue",
-                 "rlsim_probe_wall_clock_khz", "rlsim_probe_fill")
+                 "rlsim_probe_wall_clock_khz", "rlsim_probe_fill", "rlsim_probe_dispatch")
 ISSUE_KINDS = ("fma", "select_fma", "exp", "rcp", "mfma", "mixed", "mul", "fma_shared", "replay_tree", "replay_flat")
+
+
+class Dispatch(ctypes.Structure):
+    """rlsim_dispatch: the kernel form of a call."""
+    _fields_ = [("register_words", ctypes.c_uint32)]
 
 
 def _load():
@@ -33,6 +37,8 @@ def _load():
     L.rlsim_probe_wall_clock_khz.restype = ctypes.c_int
     L.rlsim_probe_fill.argtypes = [ctypes.c_uint64, u32, vp, vp]
     L.rlsim_probe_fill.restype = ctypes.c_int
+    L.rlsim_probe_dispatch.argtypes = [u32, u32, u32, u32, u32, ctypes.POINTER(Dispatch)]
+    L.rlsim_probe_dispatch.restype = ctypes.c_int
     return L
 
 
@@ -109,3 +115,13 @@ def probe_fill(dst, per_thread: int, stream=None) -> None:
     rc = probe_lib.rlsim_probe_fill(dst.numel() // 4, int(per_thread), _ptr(dst), st)
     if rc != 0:
         raise ValueError(f"rlsim_probe_fill rejected its arguments (status {rc})")
+
+
+def probe_dispatch(n: int, D: int, K: int, trajectory: bool = True, cus: int = 256) -> Dispatch:
+    """The kernel form of a K-step call on n environments with D padding words;
+    raises ValueError on a rejected argument."""
+    out = Dispatch()
+    rc = probe_lib.rlsim_probe_dispatch(int(n), int(D), int(K), int(trajectory), int(cus), ctypes.byref(out))
+    if rc != 0:
+        raise ValueError(f"rlsim_probe_dispatch rejected its arguments (status {rc})")
+    return out

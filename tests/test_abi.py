@@ -223,6 +223,11 @@ def test_probe_library_exports_and_rejects_bad_arguments():
     assert L.rlsim_probe_fill(16, (1 << 20) + 1, 16, None) == -1
     assert L.rlsim_probe_fill(1 << 40, 1, 16, None) == -1              # grid of 2^32 workgroups
     assert L.rlsim_probe_fill(16, 1, None, None) == -1
+    out = probe.Dispatch()
+    assert L.rlsim_probe_dispatch(0, 0, 1, 1, 256, out) == -1
+    assert L.rlsim_probe_dispatch(1, 0, 0, 1, 256, out) == -1
+    assert L.rlsim_probe_dispatch(1, 0, 1, 1, 0, out) == -1
+    assert L.rlsim_probe_dispatch(1, 0, 1, 1, 256, None) == -1
     assert L.rlsim_probe_fill(16, 1, 20, None) == -1                  # misaligned dst
 
 

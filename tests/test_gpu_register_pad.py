@@ -22,3 +22,19 @@ def test_register_words(D):
     assert_bit_equal(got, ref)
     for a, b in zip(got["stats"], ref["stats"]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("D", [17, 24, 28])
+def test_32_register_words_for_fewer(D):
+    """A stored rollout long enough for the 32-word form (262,145 environments,
+    more than four workgroups per CU of 256, 2^23 rows and more)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2207_07736_amd.probe import probe_dispatch
+    n, K = 262145, 32
+    assert probe_dispatch(n, D, K).register_words == 32
+    cfg = workloads.cartpole(pad_a_low=-0.5, pad_a_high=0.99, pad_b_low=-3.0, pad_b_high=0.25, max_episode_steps=13)
+    got = gpu_run(n, K, [K], D=D, seed=4, cfg=cfg)
+    ref = oracle_run(n, K, [K], D=D, seed=4, cfg=cfg)
+    assert_bit_equal(got, ref)
+    assert np.array_equal(got["stats"][0], ref["stats"][0])
