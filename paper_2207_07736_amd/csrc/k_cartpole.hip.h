@@ -35,67 +35,13 @@ struct StepArgs {
     float* reward;       // [K][n]
     uint8_t* done;       // [K][n]
     uint32_t* stats;     // [ceil(n/256)][4]
-    uint32_t* stats_acc; // [ceil(n/256)][8] accumulators of workgroups that share a row of stats, zero between calls
-    uint32_t wide_log2;  // wide kernel: log2 of a block's environments, 3 .. 8
-    float pad_a_lo, pad_a_width, pad_b_lo, pad_b_width;    // the draw behind pad_a and pad_b
 };
-// The pointers that every kernel reads stay together, so that one 64-byte scalar
-// load brings most of them: four members between pad_b and obs made the kernels
-// with padding words in registers 2-5 % slower (16,384 envs, D = 32, K = 64: 35.1
-// against 36.9 us).
-static_assert(offsetof(StepArgs, stats) == offsetof(StepArgs, cart) + 9 * sizeof(void*),
-              "new members of StepArgs go behind stats");
-
-// The padding parameters a_j, b_j of word j of global environment gid, drawn
-// again instead of loaded: Philox(gid, j, PARAMS) as k_reset_pad draws them, with
-// gid wave-uniform.  The first rounds of a counter of which only j differs
-// between lanes are mostly uniform (plain operators there, so that they run on
-// the scalar unit once per environment), and the last ones compute only what
-// the two words read: 15 vector multiplies instead of 20.  About 130 VALU cycles
-// per 64 words, where loading the 8 bytes takes 236 cycles of the SIMD's share
-// of memory bandwidth.
-__device__ __forceinline__ void draw_pad_params(const StepArgs& a, uint32_t gid, uint32_t j, float& pa, float& pb)
-{
-    constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
-    uint32_t k0 = a.p.key0, k1 = a.p.key1;
-    const auto hi = [](uint64_t v) { return (uint32_t)(v >> 32); };
-    // rounds 0-2; s.. wave-uniform, c.. per lane
-    constexpr uint64_t q = (uint64_t)M1 * (uint32_t)STREAM_PARAMS;
-    const uint64_t s0 = (uint64_t)M0 * gid;
-    uint32_t c0 = j ^ ((uint32_t)(q >> 32) ^ k0);
-    const uint32_t s2 = hi(s0) ^ k1, s3 = (uint32_t)s0;
-    k0 += W0;
-    k1 += W1;
-    const uint64_t p1 = (uint64_t)M0 * c0, s1 = (uint64_t)M1 * s2;
-    const uint32_t t0 = hi(s1) ^ (uint32_t)q ^ k0;
-    uint32_t c2 = hi(p1) ^ (s3 ^ k1), c3 = (uint32_t)p1;
-    k0 += W0;
-    k1 += W1;
-    const uint64_t s4 = (uint64_t)M0 * t0, p2 = (uint64_t)M1 * c2;
-    c0 = hi(p2) ^ ((uint32_t)s1 ^ k0);
-    uint32_t c1 = (uint32_t)p2;
-    c2 = c3 ^ (hi(s4) ^ k1);
-    c3 = (uint32_t)s4;
-    k0 += W0;
-    k1 += W1;
-#pragma unroll
-    for (int r = 3; r < 8; ++r) {
-        const uint64_t a0 = (uint64_t)M0 * c0, a1 = (uint64_t)M1 * c2;
-        c0 = __builtin_amdgcn_bitop3_b32(hi(a1), c1, k0, 0x96);
-        c2 = __builtin_amdgcn_bitop3_b32(hi(a0), c3, k1, 0x96);
-        c1 = (uint32_t)a1;
-        c3 = (uint32_t)a0;
-        k0 += W0;
-        k1 += W1;
-    }
-    // round 8: words 1 and 2; round 9: words 0 and 1
-    c1 = M1 * c2;
-    c2 = __builtin_amdgcn_bitop3_b32(hi((uint64_t)M0 * c0), c3, k1, 0x96);
-    k0 += W0;
-    const uint64_t last = (uint64_t)M1 * c2;
-    pa = uniform01_to(hi(last) ^ c1 ^ k0, a.pad_a_lo, a.pad_a_width);
-    pb = uniform01_to((uint32_t)last, a.pad_b_lo, a.pad_b_width);
-}
+// The pointers and the launch's size, which follows the arguments, share two
+// 64-byte lines that every wave loads first.  Eight more members here cost
+// one-step launches of 16,384 environments 3.5 % (median over D = 1 .. 32; 16-step
+// ones 2 %), and members between the pointers up to 5 % (D = 32, K = 64: 35.1
+// against 36.9 us).  What one kernel needs beside these has a struct of its own.
+static_assert(sizeof(StepArgs) == 176 && offsetof(StepArgs, stats) == 168, "StepArgs keeps its size and order");
 
 // The word of an action block that holds the 32 action bits of steps
 // 32q .. 32q+31 (least significant bit first).

@@ -52,6 +52,7 @@ struct PolicyArgs {
     float* p0;          // [K][n] or null
     float* logp;        // [K][n] or null
     float* value;       // [K][n] or null
+    uint32_t* stats_acc;    // [ceil(n/256)][8] accumulators of workgroups that share a row of stats, zero between calls
 };
 
 // log pi(a) for two logits, from d = l1 - l0: with z = l_other - l_a,
@@ -754,7 +755,7 @@ void k_policy_fused(StepArgs a, PolicyArgs w)
             constexpr uint32_t kShare = (uint32_t)kBlock / (F::kEnvs * (kBlock / 64));     // workgroups per block
             const uint32_t groups = (a.n + kBlock / kShare - 1u) / (kBlock / kShare);
             const uint32_t b256 = blk / kShare;
-            share_block_stats(a.stats, a.stats_acc, b256, min(kShare, groups - b256 * kShare), c0, c1, c2, c3);
+            share_block_stats(a.stats, w.stats_acc, b256, min(kShare, groups - b256 * kShare), c0, c1, c2, c3);
         }
     }
 }

@@ -17,6 +17,61 @@ namespace rlsim_dev {
 // ---------------------------------------------------------------------------
 // Wide padding.
 // ---------------------------------------------------------------------------
+struct WideArgs : StepArgs {
+    uint32_t* stats_acc; // [ceil(n/256)][8] accumulators of blocks that share a row of stats, zero between calls
+    uint32_t wide_log2;  // log2 of a block's environments, 3 .. 8
+    float pad_a_lo, pad_a_width, pad_b_lo, pad_b_width;    // the draw behind pad_a and pad_b
+};
+
+// The padding parameters a_j, b_j of word j of global environment gid, drawn
+// again instead of loaded: Philox(gid, j, PARAMS) as k_reset_pad draws them, with
+// gid wave-uniform.  The first rounds of a counter of which only j differs
+// between lanes are mostly uniform (plain operators there, so that they run on
+// the scalar unit once per environment), and the last ones compute only what
+// the two words read: 15 vector multiplies instead of 20.
+__device__ __forceinline__ void draw_pad_params(const WideArgs& a, uint32_t gid, uint32_t j, float& pa, float& pb)
+{
+    constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
+    uint32_t k0 = a.p.key0, k1 = a.p.key1;
+    const auto hi = [](uint64_t v) { return (uint32_t)(v >> 32); };
+    // rounds 0-2; s.. wave-uniform, c.. per lane
+    constexpr uint64_t q = (uint64_t)M1 * (uint32_t)STREAM_PARAMS;
+    const uint64_t s0 = (uint64_t)M0 * gid;
+    uint32_t c0 = j ^ ((uint32_t)(q >> 32) ^ k0);
+    const uint32_t s2 = hi(s0) ^ k1, s3 = (uint32_t)s0;
+    k0 += W0;
+    k1 += W1;
+    const uint64_t p1 = (uint64_t)M0 * c0, s1 = (uint64_t)M1 * s2;
+    const uint32_t t0 = hi(s1) ^ (uint32_t)q ^ k0;
+    uint32_t c2 = hi(p1) ^ (s3 ^ k1), c3 = (uint32_t)p1;
+    k0 += W0;
+    k1 += W1;
+    const uint64_t s4 = (uint64_t)M0 * t0, p2 = (uint64_t)M1 * c2;
+    c0 = hi(p2) ^ ((uint32_t)s1 ^ k0);
+    uint32_t c1 = (uint32_t)p2;
+    c2 = c3 ^ (hi(s4) ^ k1);
+    c3 = (uint32_t)s4;
+    k0 += W0;
+    k1 += W1;
+#pragma unroll
+    for (int r = 3; r < 8; ++r) {
+        const uint64_t a0 = (uint64_t)M0 * c0, a1 = (uint64_t)M1 * c2;
+        c0 = __builtin_amdgcn_bitop3_b32(hi(a1), c1, k0, 0x96);
+        c2 = __builtin_amdgcn_bitop3_b32(hi(a0), c3, k1, 0x96);
+        c1 = (uint32_t)a1;
+        c3 = (uint32_t)a0;
+        k0 += W0;
+        k1 += W1;
+    }
+    // round 8: words 1 and 2; round 9: words 0 and 1
+    c1 = M1 * c2;
+    c2 = __builtin_amdgcn_bitop3_b32(hi((uint64_t)M0 * c0), c3, k1, 0x96);
+    k0 += W0;
+    const uint64_t last = (uint64_t)M1 * c2;
+    pa = uniform01_to(hi(last) ^ c1 ^ k0, a.pad_a_lo, a.pad_a_width);
+    pb = uniform01_to((uint32_t)last, a.pad_b_lo, a.pad_b_width);
+}
+
 constexpr uint32_t kChunk = 512;                 // steps per phase-1/phase-2 round
 constexpr uint32_t kChunkWords = kChunk / 32u;   // 32-bit bit words per env per round
 
@@ -240,7 +295,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // the placement of replay_env (float4 i / 4 at word base + 64 i).  The row's tail
 // words past D keep the zero parameters they have in memory.
 template <int W>
-__device__ __forceinline__ void draw_lane_params(const StepArgs& a, uint32_t gid, uint32_t base, float (&pa)[W],
+__device__ __forceinline__ void draw_lane_params(const WideArgs& a, uint32_t gid, uint32_t base, float (&pa)[W],
                                                  float (&pb)[W])
 {
 #pragma unroll
@@ -258,7 +313,7 @@ __device__ __forceinline__ void draw_lane_params(const StepArgs& a, uint32_t gid
 // blk): W words per lane per environment, loaded as float4 with the placement
 // of replay_env.
 template <int W, int E, bool DRAW>
-__device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
+__device__ __forceinline__ void replay_group(const WideArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
                                              uint32_t steps, uint32_t blk, uint32_t col0)
 {
     static_assert(W % 4 == 0 && (E == 2 || E == 4), "bad multi-environment replay shape");
@@ -341,7 +396,7 @@ __device__ __forceinline__ void replay_group(const StepArgs& a, const uint32_t* 
 // is a scalar branch and one FMA or multiply per word.  replay_env replays
 // chunk c of column col of block blk.
 template <int W, bool DRAW>
-__device__ __forceinline__ void replay_env(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
+__device__ __forceinline__ void replay_env(const WideArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
                                            uint32_t steps, uint32_t blk, uint32_t col, uint32_t c)
 {
     static_assert(W % 4 == 0, "bad wide-padding shape");
@@ -510,7 +565,7 @@ __device__ __forceinline__ void replay_jt(float (&s)[8], const float (&pa)[8], c
 // Phase 2 of group g (columns 8 g .. 8 g + 7 of block blk): lane l holds word
 // l of each of the eight environments.  Row addresses are recomputed at the
 // store rather than held through the replay (fewer live registers).
-__device__ __forceinline__ void replay_group_jt(const StepArgs& a, const uint8_t* lds_u, const uint8_t* lds_d,
+__device__ __forceinline__ void replay_group_jt(const WideArgs& a, const uint8_t* lds_u, const uint8_t* lds_d,
                                                 uint32_t steps, uint32_t blk, uint32_t g)
 {
     const uint32_t lane = threadIdx.x % 64u;
@@ -603,7 +658,7 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t row, uint32_t 
 // Phase 2 of columns col0 .. col0 + E - 1 of block blk: lane l holds words
 // W l .. W l + W - 1 of each environment.
 template <int W, int E, bool DRAW>
-__device__ __forceinline__ void replay_masked(const StepArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
+__device__ __forceinline__ void replay_masked(const WideArgs& a, const uint32_t* lds_u, const uint32_t* lds_d,
                                               uint32_t steps, uint32_t blk, uint32_t col0)
 {
     static_assert(W == 1 || W == 2, "words per lane");
@@ -692,7 +747,7 @@ __device__ __forceinline__ void replay_masked(const StepArgs& a, const uint32_t*
 // D = 512 2.00-2.04 against 2.17-2.29 ms).
 template <int W, int E, int NW, bool DRAW, bool REC, bool STATS>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8)))
-void k_cartpole_wide(StepArgs a)
+void k_cartpole_wide(WideArgs a)
 {
     static_assert(NW >= 8 && NW <= 16, "the pipeline needs four stepping waves and at least four more");
     static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16, "shapes that fit 64 VGPRs");

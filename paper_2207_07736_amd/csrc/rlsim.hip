@@ -255,7 +255,7 @@ uint32_t wide_log2(uint32_t n, uint32_t cus)
 }
 
 template <bool DRAW, bool REC, bool STATS>
-void launch_wide(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s)
+void launch_wide(const WideArgs& a, dim3 grid, dim3 block, hipStream_t s)
 {
     if (a.D <= 64u) hipLaunchKernelGGL((k_cartpole_wide<1, 8, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
     else if (a.D <= 128u) hipLaunchKernelGGL((k_cartpole_wide<2, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
@@ -265,8 +265,9 @@ void launch_wide(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s)
 }
 
 template <bool REC, bool STATS>
-hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s)
+hipError_t launch_step(const WideArgs& args, bool wide, uint32_t cus, hipStream_t s)
 {
+    const StepArgs& a = args;
     const dim3 grid(grid_for(a.n)), block(kBlock);
     if (!wide) {
         const uint32_t words = register_words(a.D, a.n, a.K, REC, cus);
@@ -295,7 +296,7 @@ hipError_t launch_step(const StepArgs& a, bool wide, uint32_t cus, hipStream_t s
         // last one, and 11.9-12.4 ms at D = 4,096 with 64 words at two waves).
         // Every shape fits the 64 VGPRs of eight waves per SIMD: two persistent
         // 16-wave workgroups per CU.
-        StepArgs b = a;
+        WideArgs b = args;
         b.wide_log2 = wide_log2(a.n, cus);
         const dim3 grid2(min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus)), block2(1024);
         if (draw_params(a.n, a.Dp, a.K)) launch_wide<true, REC, STATS>(b, grid2, block2, s);
@@ -577,7 +578,7 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
         h->t += K;
         return RLSIM_OK;
     }
-    StepArgs a{};
+    WideArgs a{};
     a.p = h->dp;
     a.n = h->n;
     a.D = h->D;
@@ -603,7 +604,7 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
     a.stats_acc = h->stats_acc;
     if (policy) {
         PolicyArgs w{policy->w1, policy->b1, policy->w2, policy->b2, policy->w3, policy->b3,
-                     policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value};
+                     policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value, h->stats_acc};
         e = launch_policy_form(a, w, policy->dtype == RLSIM_BF16, rec, stats, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "rlsim_step_fused: launch");
         h->t += K;
