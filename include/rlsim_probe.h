@@ -138,6 +138,8 @@ int rlsim_probe_fill(uint64_t n4, uint32_t per_thread, float* dst, void* stream)
  * results). */
 typedef struct {
     uint32_t register_words;   /* D <= 32: padding words a thread holds (0: none) */
+    uint32_t wide_block;       /* D > 32: environments in a block (8 .. 256) */
+    uint32_t wide_drawn;       /* D > 32: 1 if the padding parameters are drawn again, 0 if loaded */
 } rlsim_dispatch;
 
 /* Fill *out (HOST memory); runs nothing on a device.  Errors: -1 if n == 0,

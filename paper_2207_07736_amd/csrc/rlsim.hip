@@ -219,48 +219,14 @@ constexpr uint32_t kSplitPadMinSteps = 64u;
 // (row offsets, chunk counts) far from overflow.
 constexpr uint32_t kMaxStateWords = (1u << 24) + 4u;
 
-// Whether the wide kernel draws the padding parameters again instead of loading
-// them.  Short launches are bound by the bytes of the state, long ones by the
-// replay's updates, to which the draw adds; and a state that fits the 256 MB
-// last-level cache between calls loads faster than it draws.  Loaded / drawn, us
-// a launch, by the megabytes of the three arrays:
-//          D x envs                K = 1        K = 16       K = 64
-//   120    200 x  50,000         28 / 32       36 / 39       65 / 71
-//   126     40 x 262,144         34 / 37       56 / 60      138 / 143
-//   157    200 x  65,536         35 / 33       44 / 40       69 / 74
-//   201   4096 x   4,096         44 / 33       50 / 42       70 / 74
-//   240    400 x  50,000         56 / 50       65 / 60       88 / 101
-//   315    200 x 131,072         66 / 51       80 / 67      148 / 130
-//   600   1000 x  50,000        173 / 95      178 / 108     203 / 167
-// D = 512, 262,144 envs, K = 128: 655 / 600; D = 4,096, 73,242 envs: 1,544 / 1,573.
-bool draw_params(uint32_t n, uint32_t Dp, uint32_t K)
-{
-    const uint64_t bytes = 12ull * n * Dp;
-    return K <= (bytes < 150000000ull ? 0u : bytes < 300000000ull ? 32u : 96u);
-}
-
-// log2 of the environments in a block of the wide kernel: as few (down to the
-// jump table's eight) as still give every block a resident workgroup of its
-// own, 256 beyond that.  Blocks of 64 and more fill whole stepping waves and go
-// two to a CU; smaller ones leave lanes empty, and two per CU would step twice
-// the waves.  256 per block / this rule, us a launch: 1,024 envs D = 4,096
-// K = 1 161 / 13, K = 500 2,490 / 262, D = 40 K = 500 302 / 246; 20,011 envs
-// D = 400 K = 500 519 / 326; 65,536 envs D = 200 K = 500 412 / 387.  4,096 envs,
-// D = 200, 512 blocks of 8 / 256 of 16: K = 1 9.9 / 7.8, K = 500 263 / 225.
-uint32_t wide_log2(uint32_t n, uint32_t cus)
-{
-    uint32_t l = 3u;
-    while (l < 8u && ((n - 1u) >> l) + 1u > (l < 6u ? cus : 2u * cus)) ++l;
-    return l;
-}
-
 template <bool DRAW, bool REC, bool STATS>
 void launch_wide(const WideArgs& a, dim3 grid, dim3 block, hipStream_t s)
 {
-    if (a.D <= 64u) hipLaunchKernelGGL((k_cartpole_wide<1, 8, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
-    else if (a.D <= 128u) hipLaunchKernelGGL((k_cartpole_wide<2, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
-    else if (a.D <= 256u) hipLaunchKernelGGL((k_cartpole_wide<4, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
-    else if (a.D <= 512u) hipLaunchKernelGGL((k_cartpole_wide<8, 2, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    const uint32_t lane_words = wide_lane_words(a.D);
+    if (lane_words == 1u) hipLaunchKernelGGL((k_cartpole_wide<1, 8, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else if (lane_words == 2u) hipLaunchKernelGGL((k_cartpole_wide<2, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else if (lane_words == 4u) hipLaunchKernelGGL((k_cartpole_wide<4, 4, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
+    else if (lane_words == 8u) hipLaunchKernelGGL((k_cartpole_wide<8, 2, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_cartpole_wide<16, 1, 16, DRAW, REC, STATS>), grid, block, 0, s, a);
 }
 
@@ -299,7 +265,7 @@ hipError_t launch_step(const WideArgs& args, bool wide, uint32_t cus, hipStream_
         WideArgs b = args;
         b.wide_log2 = wide_log2(a.n, cus);
         const dim3 grid2(min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus)), block2(1024);
-        if (draw_params(a.n, a.Dp, a.K)) launch_wide<true, REC, STATS>(b, grid2, block2, s);
+        if (wide_draws(a.n, a.Dp, a.K)) launch_wide<true, REC, STATS>(b, grid2, block2, s);
         else launch_wide<false, REC, STATS>(b, grid2, block2, s);
     }
     return hipGetLastError();

@@ -68,7 +68,12 @@ extern "C" int rlsim_probe_dispatch(uint32_t n, uint32_t D, uint32_t K, uint32_t
     using namespace rlsim_dev;
     if (n == 0u || K == 0u || cus == 0u || !out) return -1;
     *out = rlsim_dispatch{};
-    if (D <= kMaxRegisterWords) out->register_words = register_words(D, n, K, trajectory != 0u, cus);
+    if (D <= kMaxRegisterWords) {
+        out->register_words = register_words(D, n, K, trajectory != 0u, cus);
+    } else {
+        out->wide_block = 1u << wide_log2(n, cus);
+        out->wide_drawn = wide_draws(n, (D + 3u) & ~3u, K) ? 1u : 0u;
+    }
     return 0;
 }
 

@@ -17,7 +17,7 @@ ISSUE_KINDS = ("fma", "select_fma", "exp", "rcp", "mfma", "mixed", "mul", "fma_s
 
 class Dispatch(ctypes.Structure):
     """rlsim_dispatch: the kernel form of a call."""
-    _fields_ = [("register_words", ctypes.c_uint32)]
+    _fields_ = [(name, ctypes.c_uint32) for name in ("register_words", "wide_block", "wide_drawn")]
 
 
 def _load():

@@ -32,3 +32,46 @@ def test_long_stored_rollouts_keep_32_words(D, few):
     assert words(1048576, 500, traj=False) == few
     # on a quarter of the CUs the workgroups per CU change with them
     assert words(16385, 2000, cus=64) == 32 and words(16384, 2000, cus=64) == few
+
+
+def test_wide_blocks_give_every_block_a_workgroup():
+    """The fewest environments (8 to 256) whose blocks fit one workgroup per CU, two
+    from 64 environments a block on."""
+    def block(n, cus=256):
+        return probe_dispatch(n, 100, 1, cus=cus).wide_block
+    assert block(1) == block(2048) == 8 and block(2049) == 16 and block(8192) == 32 and block(8193) == 64
+    assert block(32768) == 64 and block(32769) == block(65536) == 128
+    assert block(65537) == block(1 << 30) == 256
+    assert block(2048, cus=64) == 32 and block(16384, cus=64) == 128
+
+
+def _draws(n, D, K):
+    return bool(probe_dispatch(n, D, K).wide_drawn)
+
+
+@pytest.mark.parametrize("D", [64, 128, 256, 512, 1000, 4096])
+def test_wide_parameters_drawn_for_short_calls_on_large_states(D):
+    """Full rows: from 160, 220, 250 and 300 MB for calls of up to 8, 32, 64 and 96
+    steps."""
+    n = {mb: -(-mb * 1000000 // (12 * D)) for mb in (160, 220, 250, 300)}
+    slack = 1.03 if D == 1000 else 1.0          # 1,000 of 1,024 words in use
+    for mb, K in ((160, 8), (220, 32), (250, 64), (300, 96)):
+        big, small = int(n[mb] * slack) + 1, int(n[mb] * 0.99)
+        assert _draws(big, D, 1) and _draws(big, D, K) and not _draws(small, D, K)
+        assert not _draws(big, D, K + 1)
+    assert not _draws(1 << 24, D, 97)
+
+
+@pytest.mark.parametrize("n,D,K", [
+    (131072, 129, 1), (131072, 129, 32), (65536, 300, 32), (131072, 100, 32), (262144, 513, 64), (262144, 65, 1),
+    (20011, 1100, 1), (20011, 1100, 32), (50000, 513, 32), (50000, 1100, 64), (50000, 1100, 96), (131072, 1100, 96),
+    (262144, 700, 96), (262144, 96, 96)])
+def test_wide_parameters_loaded_where_rows_fill_their_lanes_badly(n, D, K):
+    """Measured 5 to 30 % faster loaded: the last chunk of a row is drawn whole."""
+    assert not _draws(n, D, K)
+
+
+@pytest.mark.parametrize("n,D,K", [
+    (262144, 512, 1), (262144, 4096, 1), (131072, 513, 8), (65536, 400, 32), (131072, 512, 64), (65536, 1000, 96)])
+def test_wide_parameters_drawn_where_that_was_measured_faster(n, D, K):
+    assert _draws(n, D, K)

@@ -21,16 +21,42 @@ def test_loaded_parameters(D):
     _against_oracle(261, D, [1, 96, 97, 3, 600, 2])
 
 
-@pytest.mark.parametrize("D,megabytes,schedule", [
-    (33, 151, [1, 32]), (64, 151, [32, 33]), (65, 151, [1, 32]), (128, 151, [32, 33]), (129, 151, [1, 32]),
-    (254, 151, [32, 33]), (511, 151, [1, 32]), (513, 151, [32, 33]), (2051, 151, [1, 33]), (300, 301, [33])])
-def test_drawn_and_loaded_parameters(D, megabytes, schedule):
-    """States just above the two sizes (12 bytes a word) from which calls of up
-    to 32 and up to 96 steps draw."""
+@pytest.mark.parametrize("D", [33, 64, 65, 128, 129, 254, 300, 511, 513, 1027, 2051])
+@pytest.mark.parametrize("K", [8, 32, 64, 96])
+def test_drawn_and_loaded_parameters(D, K):
+    """The smallest state on which calls of K steps draw: calls of K and of one step
+    draw and those of K + 1 load, over environments of the first, a middle and the
+    ragged last block."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    Dp = (D + 3) // 4 * 4
-    _against_oracle(megabytes * 1000000 // (12 * Dp) + 1, D, schedule)
+    from paper_2207_07736_amd.probe import probe_dispatch
+
+    def draws(n, k):
+        return bool(probe_dispatch(n, D, k).wide_drawn)
+
+    lo, hi = 1, 1 << 20
+    if not draws(hi, K):
+        # rows that fill their lanes too badly for calls this long
+        assert K > 32 and D in (33, 65, 129, 300, 513, 1027, 2051)
+        return
+    while lo < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if draws(mid, K) else (mid + 1, hi)
+    n = lo + 1 - lo % 2                     # odd: a ragged last block
+    schedule = [K, K + 1, 1]
+    assert [draws(n, k) for k in schedule] == [True, False, True]
+    _slices_against_oracle(n, D, schedule)
+
+
+def _slices_against_oracle(n, D, schedule):
+    seed, env0 = (1 << 33) + 5, 512
+    cfg = workloads.cartpole(pad_a_low=-0.5, pad_a_high=0.99, pad_b_low=-3.0, pad_b_high=0.25)
+    slices = [(0, 70), (n // 2, n // 2 + 70), (n - 261, n)]
+    got = gpu_run(n, sum(schedule), schedule, D=D, seed=seed, cfg=cfg, env0=env0, slices=slices)
+    refs = [oracle_run(b - a, sum(schedule), schedule, D=D, seed=seed, cfg=cfg, env0=env0 + a) for a, b in slices]
+    ref = {k: np.concatenate([r[k] for r in refs], axis=-1) for k in ("obs", "action", "reward", "done", "state", "ep")}
+    ref["t"] = refs[0]["t"]
+    assert_bit_equal(got, ref)
 
 
 def _against_oracle(n, D, schedule):
