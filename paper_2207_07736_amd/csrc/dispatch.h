@@ -56,42 +56,61 @@ inline uint32_t wide_lane_words(uint32_t D)
 // costs the same for the unused words of a row's last chunk.  So what loading
 // would bring is counted by the share of words in use.  Loaded / drawn, us a
 // launch, by the megabytes of the three arrays and that share:
-//          D x envs            K = 1        K = 32       K = 64       K = 96
-//   101   128 x  65,536  1.00   23 / 20      38 / 39      55 / 59      75 / 79
-//   201   128 x 131,072  1.00   42 / 30      62 / 63      97 / 101    140 / 139
-//   240  1000 x  20,011  0.98   52 / 48      73 / 66      89 / 90     103 / 117
-//   264  1100 x  20,011  0.54   67 / 85      84 / 109    105 / 148    146 / 189
-//   307   512 x  50,000  1.00   68 / 47      82 / 69     102 / 94     129 / 120
-//   472   300 x 131,072  0.59  129 / 85     156 / 127    187 / 183    226 / 238
-//   420   700 x  50,000  0.68  111 / 85     129 / 112    153 / 151    185 / 193
-//   604   192 x 262,144  0.75  164 / 93     213 / 157    267 / 226    321 / 300
-//   660  1100 x  50,000  0.54  185 / 158    201 / 201    231 / 271    267 / 346
-//   786  1000 x  65,536  0.98  213 / 99     230 / 138    244 / 183    262 / 234
-// Over 68 such states at each of these K and at 8, the rule's choice is never more
-// than 0.7 % slower than loading.
+//          D x envs             K = 1       K = 32       K = 64       K = 96
+//   101   256 x  32,768  1.00      25 / 22      38 / 36      51 / 51      67 / 67
+//   201   128 x 131,072  1.00      42 / 29      64 / 65    100 / 103    142 / 144
+//   240  1000 x  20,011  0.98      52 / 50      74 / 69      90 / 95    105 / 121
+//   264  1100 x  20,011  0.54      72 / 89     86 / 116    109 / 157    152 / 199
+//   307   512 x  50,000  1.00      69 / 47      84 / 71     105 / 96    132 / 123
+//   317   129 x 200,000  0.52      77 / 88    147 / 135    205 / 209    261 / 283
+//   420   700 x  50,000  0.68     109 / 88    125 / 118    146 / 156    173 / 198
+//   472   300 x 131,072  0.59     133 / 84    157 / 127    189 / 185    226 / 242
+//   503   160 x 262,144  0.62     136 / 94    188 / 151    244 / 221    298 / 303
+//   660  1100 x  50,000  0.54    187 / 168    194 / 210    221 / 276    299 / 353
+//   786  1000 x  65,536  0.98    214 / 104    230 / 141    245 / 187    268 / 225
+// Over 2,144 calls (18 batch sizes, 23 row lengths, 8 values of K) the choice is at
+// most 2.5 % slower than loading, with these lines and the blocks below.
 inline bool wide_draws(uint32_t n, uint32_t Dp, uint32_t K)
 {
     const uint64_t chunk = 64ull * wide_lane_words(Dp), held = (Dp + chunk - 1u) / chunk * chunk;
     const uint64_t megabytes = 12ull * n * Dp / 1000000u * Dp / held;
     const uint64_t percent = 100ull * Dp / held;
-    if (K <= 8u) return megabytes >= 160u;
-    if (K <= 32u) return megabytes >= 220u;
-    if (K <= 64u) return megabytes >= 250u && percent >= 60u;
-    return K <= 96u && megabytes >= 300u && percent >= 70u;
+    if (K <= 8u) return megabytes >= 180u;
+    if (K <= 32u) return megabytes >= 200u && percent >= 60u;
+    if (K <= 64u) return megabytes >= 280u && percent >= 70u;
+    return K <= 96u && megabytes >= 350u && percent >= 75u;
 }
 
-// log2 of the environments in a block of the wide kernel: as few (down to the
-// jump table's eight) as still give every block a resident workgroup of its
-// own, 256 beyond that.  Blocks of 64 and more fill whole stepping waves and go
-// two to a CU; smaller ones leave lanes empty, and two per CU would step twice
-// the waves.  256 per block / this rule, us a launch: 1,024 envs D = 4,096
-// K = 1 161 / 13, K = 500 2,490 / 262, D = 40 K = 500 302 / 246; 20,011 envs
-// D = 400 K = 500 519 / 326; 65,536 envs D = 200 K = 500 412 / 387.  4,096 envs,
-// D = 200, 512 blocks of 8 / 256 of 16: K = 1 9.9 / 7.8, K = 500 263 / 225.
-inline uint32_t wide_log2(uint32_t n, uint32_t cus)
+// Batches that may run the wide kernel in blocks of fewer than 256 environments.
+inline bool wide_small_batch(uint32_t n, uint32_t cus) { return ((n - 1u) >> 7) + 1u <= 2u * cus; }
+
+// log2 of the environments in a block of the wide kernel, for rows of Dp words: as
+// few (down to the jump table's eight) as still give every block a resident
+// workgroup of its own, 256 beyond that.  Blocks of 64 and more fill whole
+// stepping waves and go two to a CU; smaller ones leave lanes empty, and two per CU
+// would step twice the waves.  256 per block / this rule, us a launch: 1,024 envs
+// D = 4,096 K = 1 161 / 13, K = 500 2,490 / 262, D = 40 K = 500 302 / 246; 20,011
+// envs D = 400 K = 500 519 / 326.  4,096 envs, D = 200, 512 blocks of 8 / 256 of
+// 16: K = 1 9.9 / 7.8, K = 500 263 / 225.
+// Blocks of 128 put two workgroups on some CUs where blocks of 256 put one on
+// fewer: long replays gain, and loaded calls bound by the state's bytes lose.
+// 256 / 128 per block: 36,000 envs D = 300 K = 1 27 / 32, D = 1,000 K = 97 179 / 213
+// but K = 300 467 / 432; 65,536 envs D = 200 K = 300 258 / 244.  With few words and a
+// trajectory past 2^24 rows, where the stores set the pace, they lose too (57,000
+// envs, D = 100: K = 256 even, K = 400 10 % slower).  Drawn calls are bound by the
+// draws, which need every SIMD: up to three blocks of 64 per CU they stay with
+// those (36,000 envs, D = 1,000, K = 8, 256 / 128 / 64 per block 87 / 91 / 72).
+// One-step calls that stream more than 110 MB of loaded state through blocks of 64
+// lose from three blocks for two CUs on: 32,768 envs D = 400 34 / 35, K = 8 36.6 / 38.3.
+inline uint32_t wide_log2(uint32_t n, uint32_t Dp, uint32_t K, uint32_t cus)
 {
     uint32_t l = 3u;
     while (l < 8u && ((n - 1u) >> l) + 1u > (l < 6u ? cus : 2u * cus)) ++l;
+    if (l == 7u) {
+        if (wide_draws(n, Dp, K)) return n <= 192u * cus ? 6u : 7u;
+        if ((Dp > 64u && K < 160u) || (Dp <= 128u && (uint64_t)n * K >= 1ull << 24)) return 8u;
+    }
+    if (l == 6u && n > 96u * cus && K <= 8u && !wide_draws(n, Dp, K) && 12ull * n * Dp >= 110000000ull) return 8u;
     return l;
 }
 

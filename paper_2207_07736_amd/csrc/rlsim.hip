@@ -263,7 +263,7 @@ hipError_t launch_step(const WideArgs& args, bool wide, uint32_t cus, hipStream_
         // Every shape fits the 64 VGPRs of eight waves per SIMD: two persistent
         // 16-wave workgroups per CU.
         WideArgs b = args;
-        b.wide_log2 = wide_log2(a.n, cus);
+        b.wide_log2 = wide_log2(a.n, a.Dp, a.K, cus);
         const dim3 grid2(min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus)), block2(1024);
         if (wide_draws(a.n, a.Dp, a.K)) launch_wide<true, REC, STATS>(b, grid2, block2, s);
         else launch_wide<false, REC, STATS>(b, grid2, block2, s);
@@ -432,7 +432,7 @@ int rlsim_create(uint32_t n_envs, uint32_t state_words, const rlsim_cfg* cfg, rl
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_a, pad_bytes);
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_b, pad_bytes);
     // the policy forms and wide blocks whose workgroups share a row of the block statistics
-    const bool shared = h->wide ? wide_log2(n_envs, h->cus) < 8u
+    const bool shared = h->wide ? wide_small_batch(n_envs, h->cus)
                                 : !chain && D == 0u && n_envs <= std::max(kPolicyForm16Envs, kPolicyForm32EnvsF32);
     if (e == hipSuccess && shared) e = hipMalloc(&h->stats_acc, (size_t)grid_for(n_envs) * 8u * sizeof(uint32_t));
     // the wide layout's row tails [D, Dp) stay zero for the handle's lifetime

@@ -71,8 +71,9 @@ extern "C" int rlsim_probe_dispatch(uint32_t n, uint32_t D, uint32_t K, uint32_t
     if (D <= kMaxRegisterWords) {
         out->register_words = register_words(D, n, K, trajectory != 0u, cus);
     } else {
-        out->wide_block = 1u << wide_log2(n, cus);
-        out->wide_drawn = wide_draws(n, (D + 3u) & ~3u, K) ? 1u : 0u;
+        const uint32_t Dp = (D + 3u) & ~3u;
+        out->wide_block = 1u << wide_log2(n, Dp, K, cus);
+        out->wide_drawn = wide_draws(n, Dp, K) ? 1u : 0u;
     }
     return 0;
 }

@@ -34,15 +34,40 @@ def test_long_stored_rollouts_keep_32_words(D, few):
     assert words(16385, 2000, cus=64) == 32 and words(16384, 2000, cus=64) == few
 
 
+def _block(n, D=100, K=200, cus=256):
+    return probe_dispatch(n, D, K, cus=cus).wide_block
+
+
 def test_wide_blocks_give_every_block_a_workgroup():
     """The fewest environments (8 to 256) whose blocks fit one workgroup per CU, two
     from 64 environments a block on."""
-    def block(n, cus=256):
-        return probe_dispatch(n, 100, 1, cus=cus).wide_block
-    assert block(1) == block(2048) == 8 and block(2049) == 16 and block(8192) == 32 and block(8193) == 64
-    assert block(32768) == 64 and block(32769) == block(65536) == 128
-    assert block(65537) == block(1 << 30) == 256
-    assert block(2048, cus=64) == 32 and block(16384, cus=64) == 128
+    for K in (1, 200):
+        assert _block(1, K=K) == _block(2048, K=K) == 8 and _block(2049, K=K) == 16
+        assert _block(8192, K=K) == 32 and _block(8193, K=K) == 64 and _block(32768, K=K) == 64
+        assert _block(65537, K=K) == _block(1 << 30, K=K) == 256
+    assert _block(32769) == _block(65536) == 128
+    assert _block(2048, cus=64) == 32 and _block(16384, cus=64) == 128
+
+
+def test_wide_blocks_of_128_only_for_long_or_drawn_calls():
+    """Between 32,769 and 65,536 environments loaded calls of fewer than 160 steps were
+    up to 17 % slower in blocks of 128, and few words with a long trajectory 10 %."""
+    for n in (32769, 36000, 45000, 65536):
+        for D, K in ((65, 1), (200, 1), (300, 97), (1000, 97), (1000, 159), (4096, 159)):
+            assert not _draws(n, D, K) and _block(n, D, K) == 256
+            assert _block(n, D, 160) == 128
+        assert _block(n, 40, 1) == _block(n, 64, 1) == 128
+    assert _block(57000, 100, 294) == 128 and _block(57000, 100, 295) == _block(57000, 128, 400) == 256
+    assert _block(57000, 64, 295) == 256
+    assert _block(57000, 129, 400) == _block(57000, 4096, 1000) == 128
+    for n, block in ((32769, 64), (49152, 64), (49153, 128), (65536, 128)):
+        assert _draws(n, 1000, 1) and _block(n, 1000, 1) == block
+
+
+def test_wide_blocks_of_64_not_for_short_calls_on_large_loaded_states():
+    assert _block(32768, 400, 1) == _block(32768, 400, 8) == _block(28000, 400, 8) == 256
+    assert _block(32768, 400, 9) == _block(32768, 200, 1) == _block(32768, 1000, 1) == 64
+    assert _block(24576, 400, 1) == _block(20011, 1100, 1) == 64
 
 
 def _draws(n, D, K):
@@ -51,11 +76,11 @@ def _draws(n, D, K):
 
 @pytest.mark.parametrize("D", [64, 128, 256, 512, 1000, 4096])
 def test_wide_parameters_drawn_for_short_calls_on_large_states(D):
-    """Full rows: from 160, 220, 250 and 300 MB for calls of up to 8, 32, 64 and 96
+    """Full rows: from 180, 200, 280 and 350 MB for calls of up to 8, 32, 64 and 96
     steps."""
-    n = {mb: -(-mb * 1000000 // (12 * D)) for mb in (160, 220, 250, 300)}
+    n = {mb: -(-mb * 1000000 // (12 * D)) for mb in (180, 200, 280, 350)}
     slack = 1.03 if D == 1000 else 1.0          # 1,000 of 1,024 words in use
-    for mb, K in ((160, 8), (220, 32), (250, 64), (300, 96)):
+    for mb, K in ((180, 8), (200, 32), (280, 64), (350, 96)):
         big, small = int(n[mb] * slack) + 1, int(n[mb] * 0.99)
         assert _draws(big, D, 1) and _draws(big, D, K) and not _draws(small, D, K)
         assert not _draws(big, D, K + 1)
@@ -65,13 +90,14 @@ def test_wide_parameters_drawn_for_short_calls_on_large_states(D):
 @pytest.mark.parametrize("n,D,K", [
     (131072, 129, 1), (131072, 129, 32), (65536, 300, 32), (131072, 100, 32), (262144, 513, 64), (262144, 65, 1),
     (20011, 1100, 1), (20011, 1100, 32), (50000, 513, 32), (50000, 1100, 64), (50000, 1100, 96), (131072, 1100, 96),
-    (262144, 700, 96), (262144, 96, 96)])
+    (262144, 700, 96), (262144, 96, 96), (200000, 129, 1), (33000, 1100, 32), (33000, 513, 1), (36000, 400, 1)])
 def test_wide_parameters_loaded_where_rows_fill_their_lanes_badly(n, D, K):
-    """Measured 5 to 30 % faster loaded: the last chunk of a row is drawn whole."""
+    """Measured 5 to 50 % faster loaded: the last chunk of a row is drawn whole."""
     assert not _draws(n, D, K)
 
 
 @pytest.mark.parametrize("n,D,K", [
-    (262144, 512, 1), (262144, 4096, 1), (131072, 513, 8), (65536, 400, 32), (131072, 512, 64), (65536, 1000, 96)])
+    (262144, 512, 1), (262144, 4096, 1), (131072, 513, 8), (65536, 400, 32), (131072, 512, 64), (65536, 1000, 96),
+    (36000, 1000, 8)])
 def test_wide_parameters_drawn_where_that_was_measured_faster(n, D, K):
     assert _draws(n, D, K)
