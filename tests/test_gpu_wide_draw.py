@@ -89,7 +89,7 @@ def test_blocks_of_fewer_environments(n, D):
 
 
 @pytest.mark.parametrize("n,D,schedule,blocks", [
-    (32769, 33, [160, 5, 161], [128, 256, 128]), (40001, 130, [160, 5, 161], [128, 256, 128]),
+    (32769, 33, [160, 5, 161], [128, 128, 128]), (40001, 130, [160, 5, 161], [128, 256, 128]),
     (33000, 400, [160, 3], [128, 256]), (28001, 400, [2, 9, 1], [256, 64, 256]), (32901, 700, [8, 33], [64, 256])])
 def test_blocks_that_change_with_the_call(n, D, schedule, blocks):
     """Calls of one handle in blocks of different sizes, their statistics included."""
