@@ -18,6 +18,12 @@ namespace rlsim_dev {
 
 constexpr int kBlock = 256;          // threads per workgroup = envs per stats block
 
+// Where a kernel takes a padding parameter from.
+union PadSource {
+    const float* words;                     // the array that a reset fills
+    struct { float lo, width; } range;      // wide kernel, drawn calls: the range it was drawn from
+};
+
 struct StepArgs {
     DevParams p;
     uint32_t n;          // environments
@@ -28,8 +34,8 @@ struct StepArgs {
     float* cart;         // [4][n]   x, x_dot, theta, theta_dot
     uint32_t* ep;        // [n]      steps taken in the current episode
     float* pad_s;        // narrow: [D][n]; wide: [n][Dp]
-    const float* pad_a;
-    const float* pad_b;
+    PadSource pad_a;
+    PadSource pad_b;
     float* obs;          // [K][4][n]
     uint8_t* action;     // [K][n]
     float* reward;       // [K][n]
@@ -342,8 +348,8 @@ void k_cartpole_fused(StepArgs a)
             const bool on = (uint32_t)j < a.D;
             const size_t q = (size_t)j * a.n + env;
             pad.s[j] = on ? a.pad_s[q] : 0.0f;
-            pad.a[j] = on ? a.pad_a[q] : 0.0f;
-            pad.b[j] = on ? a.pad_b[q] : 0.0f;
+            pad.a[j] = on ? a.pad_a.words[q] : 0.0f;
+            pad.b[j] = on ? a.pad_b.words[q] : 0.0f;
         }
         core.run(a.t0, a.K, pad);
         core.store(a);
@@ -465,8 +471,8 @@ void k_cartpole_split(StepArgs a)
             const bool on = live && (uint32_t)j < a.D;
             const size_t q = (size_t)j * a.n + env;
             pad.s[j] = on ? a.pad_s[q] : 0.0f;
-            pad.a[j] = on ? a.pad_a[q] : 0.0f;
-            pad.b[j] = on ? a.pad_b[q] : 0.0f;
+            pad.a[j] = on ? a.pad_a.words[q] : 0.0f;
+            pad.b[j] = on ? a.pad_b.words[q] : 0.0f;
         }
         PadHandOver<W> ph{pad, h};
         core.run(a.t0, a.K, ph);

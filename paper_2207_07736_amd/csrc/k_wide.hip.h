@@ -20,8 +20,12 @@ namespace rlsim_dev {
 struct WideArgs : StepArgs {
     uint32_t* stats_acc; // [ceil(n/256)][8] accumulators of blocks that share a row of stats, zero between calls
     uint32_t wide_log2;  // log2 of a block's environments, 3 .. 8
-    float pad_a_lo, pad_a_width, pad_b_lo, pad_b_width;    // the draw behind pad_a and pad_b
+    uint32_t groups;     // workgroups of the launch
 };
+// All of it ends with StepArgs' last 64-byte line, and the kernel reads no launch
+// size behind it.  With a line more, one-step calls and calls of one block a
+// workgroup were 2-4 % slower (70,000 envs, D = 200, K = 160: 181 against 187 us).
+static_assert(sizeof(WideArgs) == 192, "WideArgs ends with a 64-byte line");
 
 // The padding parameters a_j, b_j of word j of global environment gid, drawn
 // again instead of loaded: Philox(gid, j, PARAMS) as k_reset_pad draws them, with
@@ -68,8 +72,8 @@ __device__ __forceinline__ void draw_pad_params(const WideArgs& a, uint32_t gid,
     c2 = __builtin_amdgcn_bitop3_b32(hi((uint64_t)M0 * c0), c3, k1, 0x96);
     k0 += W0;
     const uint64_t last = (uint64_t)M1 * c2;
-    pa = uniform01_to(hi(last) ^ c1 ^ k0, a.pad_a_lo, a.pad_a_width);
-    pb = uniform01_to((uint32_t)last, a.pad_b_lo, a.pad_b_width);
+    pa = uniform01_to(hi(last) ^ c1 ^ k0, a.pad_a.range.lo, a.pad_a.range.width);
+    pb = uniform01_to((uint32_t)last, a.pad_b.range.lo, a.pad_b.range.width);
 }
 
 constexpr uint32_t kChunk = 512;                 // steps per phase-1/phase-2 round
@@ -336,8 +340,8 @@ __device__ __forceinline__ void replay_group(const WideArgs& a, const uint32_t* 
         const size_t row = (size_t)env[e] * a.Dp;
         const uint32_t words = live[e] ? a.Dp : 0u;
         rs[e] = row_rsrc(a.pad_s + row, words);
-        ra[e] = row_rsrc(a.pad_a + row, words);
-        rb[e] = row_rsrc(a.pad_b + row, words);
+        ra[e] = row_rsrc(a.pad_a.words + row, words);
+        rb[e] = row_rsrc(a.pad_b.words + row, words);
     }
     for (uint32_t c = 0; c < n_chunks; ++c) {
         const uint32_t base = c * chunk_words + 4u * lane;
@@ -405,8 +409,8 @@ __device__ __forceinline__ void replay_env(const WideArgs& a, const uint32_t* ld
     const uint32_t env = (blk << a.wide_log2) + col;
     const size_t row = (size_t)env * a.Dp;
     const uint32_t words = env < a.n ? a.Dp : 0u;
-    const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, words), ra = row_rsrc(a.pad_a + row, words),
-                                 rb = row_rsrc(a.pad_b + row, words);
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, words), ra = row_rsrc(a.pad_a.words + row, words),
+                                 rb = row_rsrc(a.pad_b.words + row, words);
     const uint32_t base = c * chunk_words + 4u * lane;
     float s[W], pa[W], pb[W];
 #pragma unroll
@@ -577,8 +581,8 @@ __device__ __forceinline__ void replay_group_jt(const WideArgs& a, const uint8_t
         const bool on = lane_on && env0 + (uint32_t)e < a.n;
         const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
         s[e] = on ? a.pad_s[row + lane] : 0.0f;
-        pa[e] = on ? a.pad_a[row + lane] : 0.0f;
-        pb[e] = on ? a.pad_b[row + lane] : 0.0f;
+        pa[e] = on ? a.pad_a.words[row + lane] : 0.0f;
+        pb[e] = on ? a.pad_b.words[row + lane] : 0.0f;
     }
     for (uint32_t w32 = 0; w32 * 32u < steps; ++w32) {
         const uint32_t* pu = reinterpret_cast<const uint32_t*>(lds_u + g * kChunk + w32 * 32u);
@@ -670,8 +674,8 @@ __device__ __forceinline__ void replay_masked(const WideArgs& a, const uint32_t*
     for (int e = 0; e < E; ++e) {
         const size_t row = (size_t)(env0 + (uint32_t)e) * a.Dp;
         const uint32_t words = env0 + (uint32_t)e < a.n ? a.Dp : 0u;
-        const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, words), ra = row_rsrc(a.pad_a + row, words),
-                                     rb = row_rsrc(a.pad_b + row, words);
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(a.pad_s + row, words), ra = row_rsrc(a.pad_a.words + row, words),
+                                     rb = row_rsrc(a.pad_b.words + row, words);
         load_words<W>(rs, j0, s[e]);
         if (DRAW) {
 #pragma unroll
@@ -759,7 +763,7 @@ void k_cartpole_wide(WideArgs a)
     __shared__ uint32_t lds_d[2][kChunkWords * kBlock];
     __shared__ uint32_t next_group[2];
     __shared__ uint32_t blk_stats[2][4];
-    const uint32_t G = gridDim.x, wg = blockIdx.x;
+    const uint32_t G = a.groups, wg = blockIdx.x;
     const uint32_t n_blocks = ((a.n - 1u) >> a.wide_log2) + 1u;
     const uint32_t width = 1u << a.wide_log2;       // environments of a block
     const uint32_t my_blocks = wg < n_blocks ? (n_blocks - wg + G - 1u) / G : 0u;

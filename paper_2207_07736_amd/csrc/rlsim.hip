@@ -231,11 +231,12 @@ void launch_wide(const WideArgs& a, dim3 grid, dim3 block, hipStream_t s)
 }
 
 template <bool REC, bool STATS>
-hipError_t launch_step(const WideArgs& args, bool wide, uint32_t cus, hipStream_t s)
+hipError_t launch_step(const StepArgs& a, const rlsim* h)
 {
-    const StepArgs& a = args;
+    const uint32_t cus = h->cus;
+    const hipStream_t s = h->stream;
     const dim3 grid(grid_for(a.n)), block(kBlock);
-    if (!wide) {
+    if (!h->wide) {
         const uint32_t words = register_words(a.D, a.n, a.K, REC, cus);
         if (a.D == 0u && REC && a.K >= kSplitMinSteps)
             hipLaunchKernelGGL((k_cartpole_split<0, STATS>), grid, dim3(2 * kBlock), 0, s, a);
@@ -262,11 +263,21 @@ hipError_t launch_step(const WideArgs& args, bool wide, uint32_t cus, hipStream_
         // last one, and 11.9-12.4 ms at D = 4,096 with 64 words at two waves).
         // Every shape fits the 64 VGPRs of eight waves per SIMD: two persistent
         // 16-wave workgroups per CU.
-        WideArgs b = args;
+        WideArgs b{};
+        static_cast<StepArgs&>(b) = a;
+        b.stats_acc = h->stats_acc;
         b.wide_log2 = wide_log2(a.n, a.Dp, a.K, cus);
-        const dim3 grid2(min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus)), block2(1024);
-        if (wide_draws(a.n, a.Dp, a.K)) launch_wide<true, REC, STATS>(b, grid2, block2, s);
-        else launch_wide<false, REC, STATS>(b, grid2, block2, s);
+        b.groups = std::min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus);
+        const dim3 grid2(b.groups), block2(1024);
+        if (wide_draws(a.n, a.Dp, a.K)) {
+            volatile float a_w = h->cfg.pad_a_high - h->cfg.pad_a_low;
+            volatile float b_w = h->cfg.pad_b_high - h->cfg.pad_b_low;
+            b.pad_a.range = {h->cfg.pad_a_low, a_w};
+            b.pad_b.range = {h->cfg.pad_b_low, b_w};
+            launch_wide<true, REC, STATS>(b, grid2, block2, s);
+        } else {
+            launch_wide<false, REC, STATS>(b, grid2, block2, s);
+        }
     }
     return hipGetLastError();
 }
@@ -544,7 +555,7 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
         h->t += K;
         return RLSIM_OK;
     }
-    WideArgs a{};
+    StepArgs a{};
     a.p = h->dp;
     a.n = h->n;
     a.D = h->D;
@@ -554,20 +565,13 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
     a.cart = h->cart;
     a.ep = h->ep;
     a.pad_s = h->pad_s;
-    a.pad_a = h->pad_a;
-    a.pad_b = h->pad_b;
-    volatile float a_w = h->cfg.pad_a_high - h->cfg.pad_a_low;
-    volatile float b_w = h->cfg.pad_b_high - h->cfg.pad_b_low;
-    a.pad_a_lo = h->cfg.pad_a_low;
-    a.pad_a_width = a_w;
-    a.pad_b_lo = h->cfg.pad_b_low;
-    a.pad_b_width = b_w;
+    a.pad_a.words = h->pad_a;
+    a.pad_b.words = h->pad_b;
     a.obs = tr.obs;
     a.action = tr.action;
     a.reward = tr.reward;
     a.done = tr.done;
     a.stats = tr.block_stats;
-    a.stats_acc = h->stats_acc;
     if (policy) {
         PolicyArgs w{policy->w1, policy->b1, policy->w2, policy->b2, policy->w3, policy->b3,
                      policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value, h->stats_acc};
@@ -576,10 +580,10 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
         h->t += K;
         return RLSIM_OK;
     }
-    if (rec && stats) e = launch_step<true, true>(a, h->wide, h->cus, h->stream);
-    else if (rec) e = launch_step<true, false>(a, h->wide, h->cus, h->stream);
-    else if (stats) e = launch_step<false, true>(a, h->wide, h->cus, h->stream);
-    else e = launch_step<false, false>(a, h->wide, h->cus, h->stream);
+    if (rec && stats) e = launch_step<true, true>(a, h);
+    else if (rec) e = launch_step<true, false>(a, h);
+    else if (stats) e = launch_step<false, true>(a, h);
+    else e = launch_step<false, false>(a, h);
     if (e != hipSuccess) return hip_fail(h, e, "rlsim_step_fused: launch");
     h->t += K;
     return RLSIM_OK;
