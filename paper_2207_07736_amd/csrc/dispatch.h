@@ -68,17 +68,18 @@ inline uint32_t wide_lane_words(uint32_t D)
 //   503   160 x 262,144  0.62     136 / 94    188 / 151    244 / 221    298 / 303
 //   660  1100 x  50,000  0.54    187 / 168    194 / 210    221 / 276    299 / 353
 //   786  1000 x  65,536  0.98    214 / 104    230 / 141    245 / 187    268 / 225
-// Over 2,144 calls (18 batch sizes, 23 row lengths, 8 values of K) the choice is at
-// most 2.5 % slower than loading, with these lines and the blocks below.
-inline bool wide_draws(uint32_t n, uint32_t Dp, uint32_t K)
+// Above 64 steps batches whose drawn blocks hold 64 environments (wide_log2) need
+// more.  Over 2,144 calls (18 batch sizes, 23 row lengths, 8 values of K) the choice
+// is at most 3.6 % slower than loading in blocks of 256, ten calls by 2 % or more.
+inline bool wide_draws(uint32_t n, uint32_t Dp, uint32_t K, uint32_t cus)
 {
     const uint64_t chunk = 64ull * wide_lane_words(Dp), held = (Dp + chunk - 1u) / chunk * chunk;
     const uint64_t megabytes = 12ull * n * Dp / 1000000u * Dp / held;
     const uint64_t percent = 100ull * Dp / held;
     if (K <= 8u) return megabytes >= 180u;
-    if (K <= 32u) return megabytes >= 200u && percent >= 60u;
-    if (K <= 64u) return megabytes >= 280u && percent >= 70u;
-    return K <= 96u && megabytes >= 350u && percent >= 75u;
+    if (K <= 32u) return megabytes >= 190u && (Dp <= 1024u || percent >= 55u);
+    if (K <= 64u) return megabytes >= 300u && percent >= 60u;
+    return K <= 96u && megabytes >= (n <= 192u * cus ? 410u : 250u) && percent >= 75u;
 }
 
 // Batches that may run the wide kernel in blocks of fewer than 256 environments.
@@ -93,10 +94,10 @@ inline bool wide_small_batch(uint32_t n, uint32_t cus) { return ((n - 1u) >> 7) 
 // envs D = 400 K = 500 519 / 326.  4,096 envs, D = 200, 512 blocks of 8 / 256 of
 // 16: K = 1 9.9 / 7.8, K = 500 263 / 225.
 // Blocks of 128 put two workgroups on some CUs where blocks of 256 put one on
-// fewer: long replays gain, and loaded calls bound by the state's bytes lose.
-// 256 / 128 per block: 36,000 envs D = 300 K = 1 27 / 32, D = 1,000 K = 97 179 / 213
-// but K = 300 467 / 432; 65,536 envs D = 200 K = 300 258 / 244.  With few words and a
-// trajectory past 2^24 rows, where the stores set the pace, they lose too (57,000
+// fewer: loaded calls gain where the replay's steps weigh more than the row's bytes,
+// and lose where the bytes do.  256 / 128 per block: 36,000 envs D = 300 K = 1 27 / 32,
+// K = 64 80 / 73; D = 1,000 K = 97 179 / 213, K = 300 467 / 432.  With up to 128 words and
+// a trajectory past 2^24 rows, where the stores set the pace, they lose too (57,000
 // envs, D = 100: K = 256 even, K = 400 10 % slower).  Drawn calls are bound by the
 // draws, which need every SIMD: up to three blocks of 64 per CU they stay with
 // those (36,000 envs, D = 1,000, K = 8, 256 / 128 / 64 per block 87 / 91 / 72).
@@ -107,10 +108,12 @@ inline uint32_t wide_log2(uint32_t n, uint32_t Dp, uint32_t K, uint32_t cus)
     uint32_t l = 3u;
     while (l < 8u && ((n - 1u) >> l) + 1u > (l < 6u ? cus : 2u * cus)) ++l;
     if (l == 7u) {
-        if (wide_draws(n, Dp, K)) return n <= 192u * cus ? 6u : 7u;
-        if ((Dp > 64u && K < 160u) || (Dp <= 128u && (uint64_t)n * K >= 1ull << 24)) return 8u;
+        if (wide_draws(n, Dp, K, cus)) return n <= 192u * cus ? 6u : 7u;
+        if (Dp <= 128u && (uint64_t)n * K >= 1ull << 24) return 8u;
+        const uint32_t steps = Dp <= 64u ? 1u : Dp <= 128u ? 64u : Dp <= 960u ? Dp / 6u : 160u;
+        return K >= steps ? 7u : 8u;
     }
-    if (l == 6u && n > 96u * cus && K <= 8u && !wide_draws(n, Dp, K) && 12ull * n * Dp >= 110000000ull) return 8u;
+    if (l == 6u && n > 96u * cus && K <= 8u && !wide_draws(n, Dp, K, cus) && 12ull * n * Dp >= 110000000ull) return 8u;
     return l;
 }
 

@@ -269,7 +269,7 @@ hipError_t launch_step(const StepArgs& a, const rlsim* h)
         b.wide_log2 = wide_log2(a.n, a.Dp, a.K, cus);
         b.groups = std::min(((a.n - 1u) >> b.wide_log2) + 1u, 2u * cus);
         const dim3 grid2(b.groups), block2(1024);
-        if (wide_draws(a.n, a.Dp, a.K)) {
+        if (wide_draws(a.n, a.Dp, a.K, cus)) {
             volatile float a_w = h->cfg.pad_a_high - h->cfg.pad_a_low;
             volatile float b_w = h->cfg.pad_b_high - h->cfg.pad_b_low;
             b.pad_a.range = {h->cfg.pad_a_low, a_w};

@@ -73,7 +73,7 @@ extern "C" int rlsim_probe_dispatch(uint32_t n, uint32_t D, uint32_t K, uint32_t
     } else {
         const uint32_t Dp = (D + 3u) & ~3u;
         out->wide_block = 1u << wide_log2(n, Dp, K, cus);
-        out->wide_drawn = wide_draws(n, Dp, K) ? 1u : 0u;
+        out->wide_drawn = wide_draws(n, Dp, K, cus) ? 1u : 0u;
     }
     return 0;
 }

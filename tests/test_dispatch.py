@@ -50,12 +50,14 @@ def test_wide_blocks_give_every_block_a_workgroup():
 
 
 def test_wide_blocks_of_128_only_for_long_or_drawn_calls():
-    """Between 32,769 and 65,536 environments loaded calls of fewer than 160 steps were
-    up to 17 % slower in blocks of 128, and few words with a long trajectory 10 %."""
+    """Between 32,769 and 65,536 environments loaded calls whose bytes weigh more than
+    their steps were up to 17 % slower in blocks of 128, and few words with a long
+    trajectory 10 %."""
     for n in (32769, 36000, 45000, 65536):
-        for D, K in ((65, 1), (200, 1), (300, 97), (1000, 97), (1000, 159), (4096, 159)):
-            assert not _draws(n, D, K) and _block(n, D, K) == 256
-            assert _block(n, D, 160) == 128
+        for D, K in ((65, 63), (128, 63), (129, 21), (200, 32), (300, 49), (400, 65), (600, 99), (960, 159),
+                     (1000, 159), (4096, 159)):
+            assert not _draws(n, D, K) and _block(n, D, K) == 256, (n, D, K)
+            assert not _draws(n, D, K + 1) and _block(n, D, K + 1) == 128, (n, D, K)
         assert _block(n, 40, 1) == _block(n, 64, 1) == 128
     assert _block(57000, 100, 294) == 128 and _block(57000, 100, 295) == _block(57000, 128, 400) == 256
     assert _block(57000, 64, 295) == 256
@@ -70,25 +72,25 @@ def test_wide_blocks_of_64_not_for_short_calls_on_large_loaded_states():
     assert _block(24576, 400, 1) == _block(20011, 1100, 1) == 64
 
 
-def _draws(n, D, K):
-    return bool(probe_dispatch(n, D, K).wide_drawn)
+def _draws(n, D, K, cus=256):
+    return bool(probe_dispatch(n, D, K, cus=cus).wide_drawn)
 
 
 @pytest.mark.parametrize("D", [64, 128, 256, 512, 1000, 4096])
 def test_wide_parameters_drawn_for_short_calls_on_large_states(D):
-    """Full rows: from 180, 200, 280 and 350 MB for calls of up to 8, 32, 64 and 96
-    steps."""
-    n = {mb: -(-mb * 1000000 // (12 * D)) for mb in (180, 200, 280, 350)}
-    slack = 1.03 if D == 1000 else 1.0          # 1,000 of 1,024 words in use
-    for mb, K in ((180, 8), (200, 32), (280, 64), (350, 96)):
-        big, small = int(n[mb] * slack) + 1, int(n[mb] * 0.99)
-        assert _draws(big, D, 1) and _draws(big, D, K) and not _draws(small, D, K)
-        assert not _draws(big, D, K + 1)
+    """Full rows: from 180, 190, 300 and 250 MB for calls of up to 8, 32, 64 and 96
+    steps (410 MB for up to 96 in batches of up to 192 environments per CU)."""
+    for mb, K, cus in ((180, 8, 256), (190, 32, 256), (300, 64, 256), (250, 96, 1), (410, 96, 1 << 20)):
+        n = -(-mb * 1000000 // (12 * D))
+        slack = 1.03 if D == 1000 else 1.0          # 1,000 of 1,024 words in use
+        big, small = int(n * slack) + 1, int(n * 0.99)
+        assert _draws(big, D, 1, cus) and _draws(big, D, K, cus) and not _draws(small, D, K, cus)
+        assert K == 64 or not _draws(big, D, K + 1, cus)
     assert not _draws(1 << 24, D, 97)
 
 
 @pytest.mark.parametrize("n,D,K", [
-    (131072, 129, 1), (131072, 129, 32), (65536, 300, 32), (131072, 100, 32), (262144, 513, 64), (262144, 65, 1),
+    (131072, 129, 1), (131072, 129, 32), (65536, 300, 32), (131072, 100, 32), (262144, 513, 64), (131072, 65, 1),
     (20011, 1100, 1), (20011, 1100, 32), (50000, 513, 32), (50000, 1100, 64), (50000, 1100, 96), (131072, 1100, 96),
     (262144, 700, 96), (262144, 96, 96), (200000, 129, 1), (33000, 1100, 32), (33000, 513, 1), (36000, 400, 1)])
 def test_wide_parameters_loaded_where_rows_fill_their_lanes_badly(n, D, K):
