@@ -140,6 +140,8 @@ typedef struct {
     uint32_t register_words;   /* D <= 32: padding words a thread holds (0: none) */
     uint32_t wide_block;       /* D > 32: environments in a block (8 .. 256) */
     uint32_t wide_drawn;       /* D > 32: 1 if the padding parameters are drawn again, 0 if loaded */
+    uint32_t policy_envs_bf16; /* environments of a wave of the policy kernel, bf16 and */
+    uint32_t policy_envs_f32;  /* fp32 weights (D = 0): 16, 32 or 64 */
 } rlsim_dispatch;
 
 /* Fill *out (HOST memory); runs nothing on a device.  Errors: -1 if n == 0,

@@ -117,4 +117,19 @@ inline uint32_t wide_log2(uint32_t n, uint32_t Dp, uint32_t K, uint32_t cus)
     return l;
 }
 
+// Environments of a wave of the policy kernel.  Small batches leave SIMDs idle, and
+// fewer environments per wave shorten the step; large ones pay for the cart-pole
+// steps that such waves repeat.  The lines lie where the smaller form fills three
+// workgroups per CU; a fourth takes it past the next form.  K = 32 with learner
+// outputs, us a launch with 16 / 32 / 64 environments per wave, 256 CUs:
+//   bf16  4,096 envs 41 / - / 80; 49,152 81 / - / 84; 65,536 96 / - / 84
+//   fp32  4,096 envs 65 / 101 / 183; 49,152 148 / 160 / 186; 65,536 177 / 169 /
+//         186; 98,304 252 / 239 / 291; 131,072 337 / 317 / 315
+// The fp32 form with 32 is the last one whose workgroups share rows of statistics.
+inline uint32_t policy_envs(uint32_t n, bool bf16, uint32_t cus)
+{
+    if (n <= 192u * cus) return 16u;
+    return !bf16 && n <= 384u * cus ? 32u : 64u;
+}
+
 }  // namespace rlsim_dev

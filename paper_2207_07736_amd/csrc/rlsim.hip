@@ -321,16 +321,6 @@ hipError_t launch_chain_reset(const DevParams& p, uint32_t N, uint32_t n, float*
     return hipGetLastError();
 }
 
-// Which form of the policy kernel a batch runs (all give the same bits).  Small
-// batches leave SIMDs idle, and fewer environments per wave shorten the step;
-// large ones pay for the cart-pole steps that such waves repeat.  K = 32 with
-// learner outputs, us a launch with 16 / 32 / 64 environments per wave:
-//   bf16  4,096 envs 43 / 59 / 83; 49,152 86 / 91 / 87; 65,536 109 / 95 / 87
-//   fp32  4,096 envs 65 / 99 / 173; 49,152 130 / 148 / 177; 65,536 172 / 157 /
-//         178; 98,304 244 / 225 / 266; 131,072 318 / 298 / 283
-constexpr uint32_t kPolicyForm16Envs = 49152u;      // both weight types
-constexpr uint32_t kPolicyForm32EnvsF32 = 98304u;   // fp32 weights only
-
 template <class Mlp, bool REC, bool STATS>
 hipError_t launch_policy(const StepArgs& a, const PolicyArgs& w, hipStream_t s)
 {
@@ -350,14 +340,16 @@ hipError_t launch_policy_any(const StepArgs& a, const PolicyArgs& w, bool rec, b
     return launch_policy<Mlp, false, false>(a, w, s);
 }
 
-hipError_t launch_policy_form(const StepArgs& a, const PolicyArgs& w, bool bf16, bool rec, bool stats, hipStream_t s)
+hipError_t launch_policy_form(const StepArgs& a, const PolicyArgs& w, bool bf16, bool rec, bool stats, uint32_t cus,
+                              hipStream_t s)
 {
+    const uint32_t envs = policy_envs(a.n, bf16, cus);
     if (bf16) {
-        if (a.n <= kPolicyForm16Envs) return launch_policy_any<MlpBf16<WaveForm16>>(a, w, rec, stats, s);
+        if (envs == 16u) return launch_policy_any<MlpBf16<WaveForm16>>(a, w, rec, stats, s);
         return launch_policy_any<MlpBf16<WaveForm64>>(a, w, rec, stats, s);
     }
-    if (a.n <= kPolicyForm16Envs) return launch_policy_any<MlpF32<WaveForm16>>(a, w, rec, stats, s);
-    if (a.n <= kPolicyForm32EnvsF32) return launch_policy_any<MlpF32<WaveForm32>>(a, w, rec, stats, s);
+    if (envs == 16u) return launch_policy_any<MlpF32<WaveForm16>>(a, w, rec, stats, s);
+    if (envs == 32u) return launch_policy_any<MlpF32<WaveForm32>>(a, w, rec, stats, s);
     return launch_policy_any<MlpF32<WaveForm64>>(a, w, rec, stats, s);
 }
 
@@ -444,7 +436,7 @@ int rlsim_create(uint32_t n_envs, uint32_t state_words, const rlsim_cfg* cfg, rl
     if (e == hipSuccess && D) e = hipMalloc(&h->pad_b, pad_bytes);
     // the policy forms and wide blocks whose workgroups share a row of the block statistics
     const bool shared = h->wide ? wide_small_batch(n_envs, h->cus)
-                                : !chain && D == 0u && n_envs <= std::max(kPolicyForm16Envs, kPolicyForm32EnvsF32);
+                                : !chain && D == 0u && policy_envs(n_envs, false, h->cus) < 64u;
     if (e == hipSuccess && shared) e = hipMalloc(&h->stats_acc, (size_t)grid_for(n_envs) * 8u * sizeof(uint32_t));
     // the wide layout's row tails [D, Dp) stay zero for the handle's lifetime
     if (e == hipSuccess && h->wide) e = hipMemset(h->pad_s, 0, pad_bytes);
@@ -575,7 +567,7 @@ int rlsim_step_fused(rlsim_t* h, uint32_t K, const rlsim_policy* policy, const r
     if (policy) {
         PolicyArgs w{policy->w1, policy->b1, policy->w2, policy->b2, policy->w3, policy->b3,
                      policy->wv, policy->bv, tr.policy_p0, tr.logp, tr.value, h->stats_acc};
-        e = launch_policy_form(a, w, policy->dtype == RLSIM_BF16, rec, stats, h->stream);
+        e = launch_policy_form(a, w, policy->dtype == RLSIM_BF16, rec, stats, h->cus, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "rlsim_step_fused: launch");
         h->t += K;
         return RLSIM_OK;

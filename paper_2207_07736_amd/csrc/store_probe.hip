@@ -68,6 +68,8 @@ extern "C" int rlsim_probe_dispatch(uint32_t n, uint32_t D, uint32_t K, uint32_t
     using namespace rlsim_dev;
     if (n == 0u || K == 0u || cus == 0u || !out) return -1;
     *out = rlsim_dispatch{};
+    out->policy_envs_bf16 = policy_envs(n, true, cus);
+    out->policy_envs_f32 = policy_envs(n, false, cus);
     if (D <= kMaxRegisterWords) {
         out->register_words = register_words(D, n, K, trajectory != 0u, cus);
     } else {

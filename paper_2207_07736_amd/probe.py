@@ -17,7 +17,8 @@ ISSUE_KINDS = ("fma", "select_fma", "exp", "rcp", "mfma", "mixed", "mul", "fma_s
 
 class Dispatch(ctypes.Structure):
     """rlsim_dispatch: the kernel form of a call."""
-    _fields_ = [(name, ctypes.c_uint32) for name in ("register_words", "wide_block", "wide_drawn")]
+    _fields_ = [(name, ctypes.c_uint32) for name in (
+        "register_words", "wide_block", "wide_drawn", "policy_envs_bf16", "policy_envs_f32")]
 
 
 def _load():

@@ -103,3 +103,15 @@ def test_wide_parameters_loaded_where_rows_fill_their_lanes_badly(n, D, K):
     (36000, 1000, 8)])
 def test_wide_parameters_drawn_where_that_was_measured_faster(n, D, K):
     assert _draws(n, D, K)
+
+
+def test_policy_forms_follow_the_compute_units():
+    def envs(n, cus=256):
+        d = probe_dispatch(n, 0, 1, cus=cus)
+        return d.policy_envs_bf16, d.policy_envs_f32
+    assert envs(1) == envs(49152) == (16, 16)
+    assert envs(49153) == envs(98304) == (64, 32)
+    assert envs(98305) == envs(1 << 30) == (64, 64)
+    # a partition with an eighth of the CUs fills up at an eighth of the batch
+    assert envs(6144, 32) == (16, 16) and envs(6145, 32) == envs(12288, 32) == (64, 32)
+    assert envs(12289, 32) == (64, 64)
