@@ -42,7 +42,7 @@ def traffic_file(workload: str) -> str:
 
 # sources of the fused random-action kernel the headline times, and of the
 # launch code that picks it
-FUSED_KERNEL_SOURCES = ("device_common.hip.h", "k_cartpole.hip.h", "rlsim.hip")
+FUSED_KERNEL_SOURCES = ("device_common.hip.h", "dispatch.h", "k_cartpole.hip.h", "rlsim.hip")
 # the kernel a trajectory-recording launch of K >= 16 steps without padding
 # words runs (the headline launch), as rocprofv3 names it and as reported
 HEADLINE_KERNEL_PREFIX = "void rlsim_dev::k_cartpole_split<0,"
@@ -344,9 +344,7 @@ def fusion_sweeps(stream) -> dict:
         entry = {}
         for K in w["K"]:
             ms = _time_schedule(sim, traj, [K] * (T // K), stream, reps=2)
-            # short calls on large states draw the parameters a and b instead of reading them
-            drawn = D > 32 and K <= 32 and 12 * D * n >= 150_000_000
-            state_bytes = (40 + (8 if drawn else 16) * D) * n * (T // K)
+            state_bytes = padded_state_bytes(n, D, params_drawn(n, D, K)) * (T // K)
             entry[f"K{K}"] = {"ms": ms, "env_steps_per_s": n * T / (ms * 1e-3),
                               "algorithmic_GBs": (n * T * workloads.TRAJ_BYTES_PER_ENV_STEP + state_bytes) / (ms * 1e-3) / 1e9}
         ms_nt = _time_schedule(sim, None, [T], stream, reps=2)
@@ -359,9 +357,10 @@ def fusion_sweeps(stream) -> dict:
         sim.close()
         print(f"[bench] sweep D={D}: K1 {entry['K1']['ms']:.2f} ms, K500 {entry['K500']['ms']:.2f} ms", file=sys.stderr,
               flush=True)
-    # the unfused wide launches against a plain stream of the same traffic mix
+    # the unfused wide launches beside a plain stream of the loaded parameters' mix
     D = max(w["D"])
-    d_rows[f"D{D}"]["K1"]["stream_probe"] = stream_ceiling(n * D, d_rows[f"D{D}"]["K1"]["algorithmic_GBs"], stream)
+    d_rows[f"D{D}"]["K1"]["stream_probe"] = stream_ceiling(n * D, d_rows[f"D{D}"]["K1"]["algorithmic_GBs"], stream,
+                                                           params_drawn(n, D, 1))
     out[w["name"]] = d_rows
 
     out[workloads.WORKLOADS[workloads.MLP]["name"]] = policy_sweep(stream)
@@ -431,9 +430,24 @@ def chain_sweep(stream) -> dict:
     return rows
 
 
-def stream_ceiling(words: int, achieved_gbs: float, stream) -> dict:
-    """Time rlsim_probe_stream (read s, a, b; write s) over `words` fp32 words
-    per array, and the fraction of its rate that `achieved_gbs` reaches."""
+def params_drawn(n: int, D: int, K: int) -> bool:
+    """Whether a K-step call draws the padding parameters a and b again instead of
+    reading them, by the library's own rule."""
+    from paper_2207_07736_amd.probe import probe_dispatch
+    return bool(probe_dispatch(n, D, K, cus=CUS).wide_drawn)
+
+
+def padded_state_bytes(n: int, D: int, drawn: bool) -> int:
+    """Bytes of state that one call reads and writes: the cart-pole words and the
+    episode counter, the padding words, and a and b where they are read."""
+    return (40 + (8 if drawn else 16) * D) * n
+
+
+def stream_ceiling(words: int, achieved_gbs: float, stream, drawn: bool = False) -> dict:
+    """Time rlsim_probe_stream (read s, a, b; write s) over `words` fp32 words per
+    array, and the fraction of its rate that `achieved_gbs` reaches: none for a
+    launch that draws a and b, whose bytes are half reads and half writes where the
+    probe's are three reads to a write."""
     import torch
     from paper_2207_07736_amd.probe import probe_stream
     s, a, b = (torch.zeros(words, dtype=torch.float32, device="cuda") for _ in range(3))
@@ -450,7 +464,8 @@ def stream_ceiling(words: int, achieved_gbs: float, stream) -> dict:
     ms = times[len(times) // 2]
     gbs = words * 16 / (ms * 1e-3) / 1e9
     del s, a, b
-    return {"ms": ms, "GBs": gbs, "frac_of_stream_ceiling": achieved_gbs / gbs}
+    return {"ms": ms, "GBs": gbs, "params_drawn": drawn,
+            "frac_of_stream_ceiling": None if drawn else achieved_gbs / gbs}
 
 
 # iterations per launch of each instruction-rate probe kind (about 1-3 ms)

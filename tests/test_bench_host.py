@@ -65,3 +65,41 @@ def test_kernel_digest_ignores_comments_but_not_code():
     assert bench.code_text(src) == bench.code_text(src.replace("  return", "\treturn"))
     assert bench.code_text(src) != bench.code_text(src.replace("x + 1", "x + 2"))
     assert "comment" not in bench.code_text(src)
+
+
+@pytest.mark.parametrize("n,D,K,drawn", [
+    (262144, 4096, 1, True), (262144, 4096, 500, False), (262144, 16, 1, False), (262144, 513, 96, False),
+    (262144, 512, 64, True), (20011, 1100, 1, False)])
+def test_state_bytes_follow_the_librarys_choice(n, D, K, drawn):
+    """The parameters count as read where the library reads them, short rows and
+    the longer calls included."""
+    assert bench.params_drawn(n, D, K) == drawn
+    assert bench.padded_state_bytes(n, D, drawn) == n * (40 + (8 if drawn else 16) * D)
+
+
+def test_stream_fraction_only_for_the_probes_own_mix(monkeypatch):
+    """A launch that draws its parameters is not divided by the rate of a stream that
+    reads them."""
+    torch = pytest.importorskip("torch")
+    from paper_2207_07736_amd import probe
+
+    class Event:
+        def __init__(self, enable_timing):
+            pass
+
+        def record(self, stream):
+            pass
+
+        def elapsed_time(self, other):
+            return 2.0
+
+    zeros = torch.zeros
+    monkeypatch.setattr(torch, "zeros", lambda *a, **k: zeros(1))
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    monkeypatch.setattr(probe, "probe_stream", lambda *a: None)
+    loaded = bench.stream_ceiling(1000, 4.0e-3, None)
+    assert loaded["GBs"] == 1000 * 16 / 2.0e-3 / 1e9
+    assert loaded["frac_of_stream_ceiling"] == 4.0e-3 / loaded["GBs"] and not loaded["params_drawn"]
+    drawn = bench.stream_ceiling(1000, 4.0e-3, None, drawn=True)
+    assert drawn["frac_of_stream_ceiling"] is None and drawn["params_drawn"]
