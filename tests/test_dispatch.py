@@ -2,6 +2,10 @@
 rule's edges, and sizes at which the other form was measured slower."""
 import pytest
 
+# before the package, whose library binds to the HIP runtime already loaded: the GPU
+# tests of the same process share torch's
+import torch  # noqa: F401
+
 from paper_2207_07736_amd.probe import probe_dispatch
 
 
