@@ -303,7 +303,8 @@ struct NoPad {
 // the pace, and masks made once per step take the selects' place (v_bitop3_b32
 // and AND issue faster than v_cndmask_b32): D = 20, 100,003 envs, K = 128 75 ->
 // 73 us.  Masks were 0.5-1.4 % slower at 8, 12 and 16 words, where the stores
-// weigh more, and 2 % at 32 (262,144 envs, K = 128 203 against 199 us).
+// weigh more, and 2 % at 32 (262,144 envs, K = 128 203 against 199 us); at 28 they
+// gained 4 % at 100,003 envs and lost 4 % at 65,536 and 262,144.
 template <int W>
 struct RegisterPad {
     float s[W > 0 ? W : 1], a[W > 0 ? W : 1], b[W > 0 ? W : 1];

@@ -422,7 +422,8 @@ struct MlpF32 {
 #pragma unroll
         for (int M = 0; M < F::kTiles; ++M)
 #pragma unroll
-            for (int s = 0; s < F::kTileRows / 16; ++s) a1[M][s] = w1[(F::a_row(lane) + F::a_step(M)) * 4u + F::group(lane) + F::g_step(s)];
+            for (int s = 0; s < F::kTileRows / 16; ++s)
+                a1[M][s] = w1[(F::a_row(lane) + F::a_step(M)) * 4u + F::group(lane) + F::g_step(s)];
         b3_0 = w.b3 ? w.b3[0] : 0.0f;
         b3_1 = w.b3 ? w.b3[1] : 0.0f;
         bv = w.bv ? w.bv[0] : 0.0f;
@@ -480,8 +481,10 @@ struct MlpF32 {
 #pragma unroll
                 for (int M = 0; M < F::kTiles; ++M) {
                     const float w = w2[(F::a_row(lane) + F::a_step(M)) * 64u + unit], a = on ? w : 0.0f;
-                    if constexpr (F::kTileRows == 32) c2[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c2[M], 0, 0, 0);
-                    else c2[M] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c2[M], 0, 0, 0);
+                    if constexpr (F::kTileRows == 32)
+                        c2[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c2[M], 0, 0, 0);
+                    else
+                        c2[M] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c2[M], 0, 0, 0);
                 }
             }
         }
@@ -521,8 +524,9 @@ struct MlpF32 {
             for (int M = 0; M < F::kTiles; ++M) {
                 c1[M] = tab.bias(offsetof(Tables, b1), M);
                 if constexpr (F::kTileRows == 32) {
-                    c1[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[M][0], own_tile ? own[0] : other[0], c1[M], 0, 0, 0);
-                    c1[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[M][1], own_tile ? own[1] : other[1], c1[M], 0, 0, 0);
+                    const float x0 = own_tile ? own[0] : other[0], x1 = own_tile ? own[1] : other[1];
+                    c1[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[M][0], x0, c1[M], 0, 0, 0);
+                    c1[M] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[M][1], x1, c1[M], 0, 0, 0);
                 } else {
                     c1[M] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[M][0], own[0], c1[M], 0, 0, 0);
                 }

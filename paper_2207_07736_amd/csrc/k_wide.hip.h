@@ -32,7 +32,8 @@ static_assert(sizeof(WideArgs) == 192, "WideArgs ends with a 64-byte line");
 // gid wave-uniform.  The first rounds of a counter of which only j differs
 // between lanes are mostly uniform (plain operators there, so that they run on
 // the scalar unit once per environment), and the last ones compute only what
-// the two words read: 15 vector multiplies instead of 20.
+// the two words read: 15 vector multiplies instead of 20.  262,144 envs, D = 512,
+// K = 1: 417 us loaded, 217 drawn (dispatch.h has the line between them).
 __device__ __forceinline__ void draw_pad_params(const WideArgs& a, uint32_t gid, uint32_t j, float& pa, float& pb)
 {
     constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
@@ -732,15 +733,17 @@ __device__ __forceinline__ void replay_masked(const WideArgs& a, const uint32_t*
 // persistent workgroup of NW waves (two workgroups per CU; workgroup g takes
 // the blocks g, g + G, ... of a grid of G; a block is 256 environments, or
 // fewer, 2^wide_log2, in batches that would not give every CU one of 256).  A
-// work item is one 512-step round of one block, and the workgroup's items are its blocks round by round.
+// work item is one 512-step round of one block, and the workgroup's items are its
+// blocks round by round.
 // In iteration j the first four waves run phase 1 of item j (the cart-pole loop
 // with its trajectory stores, the action and done bits into LDS slot j & 1);
 // the other waves replay item j - 1 from slot (j - 1) & 1, taking
 // E-environment groups from an LDS counter; one workgroup barrier ends the
 // iteration.  The stepping waves join the replay after the workgroup's last
 // item: their cart-pole state and the replay's words then never share
-// registers, which keeps the kernel within the 64 VGPRs of eight waves per SIMD.  Phase 1 of one block thus runs beside the replay
-// of the one before it, and only the first item's phase 1 is exposed (262,144
+// registers, which keeps the kernel within the 64 VGPRs of eight waves per SIMD.
+// Phase 1 of one block thus runs beside the replay of the one before it, and only
+// the first item's phase 1 is exposed (262,144
 // envs x 500 steps against the same phases run one after the other in 256-env
 // workgroups: D = 512 2.11 against 2.45 ms, D = 2,048 6.33 against 8.59 ms).
 // Block statistics go through LDS slot m & 1 of the workgroup's m-th block and
