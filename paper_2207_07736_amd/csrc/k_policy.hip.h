@@ -384,22 +384,23 @@ struct MlpBf16 {
 };
 
 // ---------------------------------------------------------------------------
-// fp32 MLP.  What bounds it is the VALU (tanh) and the matrix pipe one after the
-// other: fp32 matrix instructions share the SIMD with fp32 vector ones.  Layer 1
-// runs on the fp32 matrix instructions and layer 3 on the VALU; layer 2, nine
+// fp32 MLP.  What bounds it is the vector work (tanh, the splits, layer 3: active for
+// 82 % of a launch) beside matrix instructions that overlap it in part (50 %); fp32
+// matrix instructions share the SIMD with fp32 vector ones and do not.  Layer 1 runs
+// on the fp32 matrix instructions and layer 3 on the VALU; layer 2, nine
 // tenths of the arithmetic, runs on the bf16 ones at 16 times the fp32 rate, with
 // every operand split into three bfloat16 pieces (8 + 8 + 8 bits, each rounded to
 // nearest: the split is exact).  Of the nine products of the pieces the one left
 // out, of the two last pieces, is at most 2^-34 of the whole.  The seven small
 // ones are within 2^-7 of it and are summed on their own, so that only the eight
 // leading sums (one a group) and the last addition round at the result's scale,
-// where 64 fp32 products summed one by one round 64 times.  Error against 64 bits,
-// the value head of eight random networks, 98,560 environments: 6.9e-8 rms with
-// fp32 products, 6.4e-8 with these; one weight per row with a bias that cancels
-// it: within 2^-30 of the product.  1,048,576 environments, K = 16, learner
-// outputs: 1.49 ms with fp32 products, 1.18 ms with these (102 -> 129 TFLOP/s of
-// the network's own arithmetic); six products (the three largest left out reach
-// 2^-24 together) took 1.04 ms.
+// where 64 fp32 products summed one by one round 64 times.  Error against 64 bits over
+// 24 random networks, 524,288 environments with swinging poles: the value head
+// 1.04e-7 rms (6.7e-7 at most) with fp32 products, 7.6e-8 (4.3e-7) with these, p0 3.9e-8
+// and 3.3e-8; one weight per row with a bias that cancels it: within 2^-30 of the
+// product.  1,048,576 environments, K = 16, learner outputs: 1.51 ms with fp32
+// products, 1.19 ms with these (102 -> 128 TFLOP/s of the network's own arithmetic);
+// six products (the three left out reach 2^-24 together) took 1.04 ms.
 // WaveForm64 takes its two column tiles one after the other: both at once need
 // 256 registers, and four waves per SIMD spill.
 // ---------------------------------------------------------------------------
