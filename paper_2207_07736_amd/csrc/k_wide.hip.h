@@ -789,9 +789,13 @@ void k_cartpole_wide(WideArgs a)
         const uint32_t blk = __builtin_amdgcn_readfirstlane(wg + m * G);
         const uint32_t k0 = r * kChunk, steps = min(kChunk, a.K - k0);
         const uint32_t cols = min(width, a.n - (blk << a.wide_log2));
-        // one environment per wave (E = 1): a group is one 64 W-word chunk of it
+        // one environment per wave (E = 1): a group is one 64 W-word chunk of it, or,
+        // with loaded parameters in blocks of 256 environments, its whole row: there
+        // are rows enough for every wave (262,144 envs x 500, D = 4,096 11.37 ms by
+        // chunks, 11.22 by rows; drawn, D = 700, K = 8 391 us by chunks, 402 by rows)
         const uint32_t n_chunks = (a.Dp + 64u * (uint32_t)W - 1u) / (64u * (uint32_t)W);
-        const uint32_t n_groups = E > 1 ? (cols + (uint32_t)E - 1u) / (uint32_t)E : cols * n_chunks;
+        const uint32_t parts = !DRAW && a.wide_log2 == 8u ? 1u : n_chunks;
+        const uint32_t n_groups = E > 1 ? (cols + (uint32_t)E - 1u) / (uint32_t)E : cols * parts;
         const uint32_t sl = i & 1u;
         for (;;) {
             uint32_t g = 0u;
@@ -803,7 +807,10 @@ void k_cartpole_wide(WideArgs a)
                                 reinterpret_cast<const uint8_t*>(lds_d[sl]), steps, blk, g);
             else if constexpr (W <= 2) replay_masked<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
             else if constexpr (E > 1) replay_group<W, E, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g * (uint32_t)E);
-            else replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g / n_chunks, g % n_chunks);
+            else if constexpr (DRAW) replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g / parts, g % parts);
+            else if (parts == 1u)
+                for (uint32_t c = 0; c < n_chunks; ++c) replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g, c);
+            else replay_env<W, DRAW>(a, lds_u[sl], lds_d[sl], steps, blk, g / parts, g % parts);
         }
     };
 
